@@ -65,8 +65,13 @@ struct SampleCache {
     int K, stride;
 };
 
-struct Seg {
-    double ts, te, C[3], A;  // t-range, premultiplied colour, opacity
+// An open supersegment: samples [qs, qe) of its ray (qs < 0: none is open),
+// premultiplied colour and opacity.  While none is open C and A are zero, so
+// that the first sample is taken by the same expressions as the later ones
+// (0 + (1 - 0) a c is a c).
+struct Open {
+    double C[3], A;
+    int qs, qe;
 };
 
 __host__ __device__ inline double clamp01(double v)
@@ -161,66 +166,164 @@ __host__ __device__ inline Sample cached_sample(const GenParams &G, const Sample
     return take_sample(G, d, t0, len, q);
 }
 
-// Split the first ns samples of a ray into supersegments with sensitivity
-// gamma (Eq. 1).  cap == 0: count only.  cap > 0: at most cap supersegments;
-// once cap - 1 are closed the last one takes every remaining non-transparent
-// sample, across gaps.  Eq. 1 compares the open supersegment's straight colour
-// times its opacity normalised to one sample length with the next sample's
-// colour times its opacity.  With WRITE, supersegment j goes to slot j of
-// list li (depths as V_O view depth f = t cos(theta), b likewise).
-template <bool WRITE>
-__host__ __device__ inline int split_ray(const GenParams &G, const SampleCache &C, const double *d, double cth, double t0,
-                                         double len, int ns, double gamma, int cap, size_t li, size_t plane,
+__host__ __device__ inline void reset(Open &o)
+{
+    o.C[0] = o.C[1] = o.C[2] = o.A = 0.0;
+    o.qs = -1;
+}
+
+__host__ __device__ inline void take(Open &o, const Sample &s, int q)
+{
+#pragma clang fp contract(off)
+    if (o.qs < 0) o.qs = q;
+    for (int m = 0; m < 3; ++m) o.C[m] += (1.0 - o.A) * s.a * s.c[m];
+    o.A += (1.0 - o.A) * s.a;
+    o.qe = q + 1;
+}
+
+// Eq. 1's distance between the open supersegment, its opacity normalised to
+// one sample length, and the next sample, in FP64, against gamma.
+__host__ __device__ inline bool far_exact(const Open &o, const Sample &s, double t0, double len, double gamma)
+{
+#pragma clang fp contract(off)
+    const double lenS = (t0 + o.qe * len) - (t0 + o.qs * len);
+    const double abar = 1.0 - gen_pow(1.0 - o.A, len / lenS);
+    double d2 = 0.0;
+    for (int m = 0; m < 3; ++m) {
+        const double e = o.C[m] / o.A * abar - s.c[m] * s.a;
+        d2 += e * e;
+    }
+    return sqrt(d2) >= gamma;
+}
+
+// The same decision with most of the FP64 left out.  The squared distance is
+// first computed in FP32 (hardware base-2 exponential, logarithm and
+// reciprocal); only when it lies within kFarErr of gamma is far_exact asked,
+// so the outcome is always far_exact's.  The bound, for a ray whose opacities
+// are at most 0.25 and whose colours lie in [0, 1] (Passes::err is NaN
+// for others, and every decision exact): with m = qe - qs samples the
+// normalised opacity is 1 - 2^(log2(1 - A) / m), where |log2(1 - A) / m| <=
+// 0.42 since it is the mean of the samples' logarithms.  Rounding 1 - A to
+// FP32 moves the exponent by at most 1e-7, the logarithm's, reciprocal's and
+// product's errors (1 ulp each) by 2e-7; with the exponential's ulp the
+// opacity is off by at most 4e-7, and the quotient C / A, its product and the
+// sample's colour add 2e-7 per channel: 1.1e-6 over three channels.  len /
+// lenS differs from 1 / m by 1e-12 at most.  kFarErr is three times that.
+// far_exact takes about 250 instructions and was two thirds of the kernel;
+// the filter takes about 30, and asks for it in less than 1% of the steps.
+constexpr float kFarErr = 3.5e-6f;
+
+#ifdef __HIP_DEVICE_COMPILE__
+__device__ inline float gen_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ inline float gen_log2(float x) { return __builtin_amdgcn_logf(x); }
+__device__ inline float gen_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+#else
+__host__ inline float gen_exp2(float x) { return exp2f(x); }
+__host__ inline float gen_log2(float x) { return log2f(x); }
+__host__ inline float gen_rcp(float x) { return 1.0f / x; }
+#endif
+
+// gamma with the squares of the FP32 distances at which far_exact's outcome
+// is certain (below lo2: false, from hi2 on: true).
+struct Sensitivity {
+    double gamma;
+    float lo2, hi2;
+};
+
+__host__ __device__ inline Sensitivity sensitivity(double gamma, float err)
+{
+    const float g = (float)gamma, lo = fmaxf(g - err, 0.0f), hi = g + err;
+    return {gamma, lo * lo, hi * hi};
+}
+
+__host__ __device__ inline bool is_far(const Open &o, const Sample &s, double t0, double len, const Sensitivity &g)
+{
+    const float a = (float)s.a;
+    const float ab = 1.0f - gen_exp2(gen_log2((float)(1.0 - o.A)) * gen_rcp((float)(o.qe - o.qs)));
+    const float k = ab * gen_rcp((float)o.A);
+    float d2 = 0.0f;
+    for (int m = 0; m < 3; ++m) {
+        const float e = (float)o.C[m] * k - (float)s.c[m] * a;
+        d2 += e * e;
+    }
+    if (d2 >= g.hi2) return true;
+    if (d2 < g.lo2) return false;
+    return far_exact(o, s, t0, len, g.gamma);  // too close to call, or not a number
+}
+
+// What the passes over a ray's samples share: its parameters, the ns samples
+// before early termination, and the filter's error bound.
+struct Passes {
+    double t0, len;
+    int ns;
+    float err;
+};
+
+// Count the supersegments of a ray at NG sensitivities in one pass (Eq. 1):
+// a sample joins the open supersegment unless it is far from it, a
+// transparent sample closes it.  The pass ends once every count exceeds `most`
+// (nothing asks by how much).  NG = 3 covers two steps of the bisection,
+// whichever way the first one goes: the samples are then read from the cache,
+// and their colours computed, half as often, and the three chains of dependent
+// FP64 operations overlap.
+template <int NG>
+__host__ __device__ inline void count_segments(const GenParams &G, const SampleCache &C, const double *d,
+                                               const Passes &P, const Sensitivity *g, int most, int *out)
+{
+#pragma clang fp contract(off)
+    Open o[NG];
+    int n[NG];
+    for (int k = 0; k < NG; ++k) {
+        reset(o[k]);
+        n[k] = 0;
+    }
+    for (int q = 0; q < P.ns; ++q) {
+        const Sample s = cached_sample(G, C, d, P.t0, P.len, q);
+        bool more = false;
+        for (int k = 0; k < NG; ++k) {
+            const bool open = o[k].qs >= 0;
+            if (open && (s.a == 0.0 || is_far(o[k], s, P.t0, P.len, g[k]))) {
+                ++n[k];
+                reset(o[k]);
+            }
+            more = more || n[k] <= most;
+            if (s.a != 0.0) take(o[k], s, q);
+        }
+        if (!more) break;
+    }
+    for (int k = 0; k < NG; ++k) out[k] = n[k] + (o[k].qs >= 0 ? 1 : 0);
+}
+
+// Split the samples of a ray into at most cap supersegments with sensitivity
+// g (Eq. 1) and write supersegment j to slot j of list li (depths as V_O view
+// depth f = t cos(theta), b likewise).  Once cap - 1 are closed the last one
+// takes every remaining non-transparent sample, across gaps.
+__host__ __device__ inline int split_ray(const GenParams &G, const SampleCache &C, const double *d, double cth,
+                                         const Passes &P, const Sensitivity &g, int cap, size_t li, size_t plane,
                                          float2 *depth, float4 *rgba)
 {
 #pragma clang fp contract(off)
-    int nclosed = 0;
-    bool open = false;
-    Seg cur = {0.0, 0.0, {0.0, 0.0, 0.0}, 0.0};
+    int n = 0;
+    Open o;
+    reset(o);
     auto close = [&]() {
-        if constexpr (WRITE) {
-            float f = (float)(cur.ts * cth), b = (float)(cur.te * cth);
-            if (!(b > f)) b = nextafterf(f, INFINITY);
-            const size_t o = (size_t)nclosed * plane + li;
-            depth[o] = make_float2(f, b);
-            const double A = cur.A;
-            rgba[o] = make_float4((float)(cur.C[0] / A), (float)(cur.C[1] / A), (float)(cur.C[2] / A), (float)A);
-        }
-        ++nclosed;
-        open = false;
+        const double ts = P.t0 + o.qs * P.len, te = P.t0 + o.qe * P.len;
+        float f = (float)(ts * cth), b = (float)(te * cth);
+        if (!(b > f)) b = nextafterf(f, INFINITY);
+        const size_t at = (size_t)n * plane + li;
+        depth[at] = make_float2(f, b);
+        const double A = o.A;
+        rgba[at] = make_float4((float)(o.C[0] / A), (float)(o.C[1] / A), (float)(o.C[2] / A), (float)A);
+        ++n;
+        reset(o);
     };
-    for (int q = 0; q < ns; ++q) {
-        const Sample s = cached_sample(G, C, d, t0, len, q);
-        const bool last = cap > 0 && nclosed == cap - 1;
-        if (s.a == 0.0) {
-            if (open && !last) close();
-            continue;
-        }
-        const double qs = t0 + q * len, qe = t0 + (q + 1) * len;
-        if (open && !last) {
-            const double lenS = cur.te - cur.ts;
-            const double abar = 1.0 - gen_pow(1.0 - cur.A, len / lenS);
-            double d2 = 0.0;
-            for (int m = 0; m < 3; ++m) {
-                const double e = cur.C[m] / cur.A * abar - s.c[m] * s.a;
-                d2 += e * e;
-            }
-            if (sqrt(d2) >= gamma) close();
-        }
-        if (!open) {
-            cur.ts = qs;
-            cur.te = qe;
-            cur.A = s.a;
-            for (int m = 0; m < 3; ++m) cur.C[m] = s.a * s.c[m];
-            open = true;
-            continue;
-        }
-        for (int m = 0; m < 3; ++m) cur.C[m] += (1.0 - cur.A) * s.a * s.c[m];
-        cur.A += (1.0 - cur.A) * s.a;
-        cur.te = qe;
+    for (int q = 0; q < P.ns; ++q) {
+        const Sample s = cached_sample(G, C, d, P.t0, P.len, q);
+        if (o.qs >= 0 && n != cap - 1 && (s.a == 0.0 || is_far(o, s, P.t0, P.len, g))) close();
+        if (s.a != 0.0) take(o, s, q);
     }
-    if (open) close();
-    return nclosed;
+    if (o.qs >= 0) close();
+    return n;
 }
 
 // Ray through the centre of pixel (px, py) of the camera, clipped to the
@@ -268,33 +371,67 @@ __host__ __device__ inline int sample_count(const GenParams &G, double t0, doubl
 }
 
 // Sensitivity of one ray (supplement Alg. S1; bracket updates as read in
-// the design notes).  count(g), the ray's supersegments at sensitivity g,
-// does not grow with g; the search wants N_S - delta <= count(g) <= N_S.
+// the design notes).  The ray's supersegments at sensitivity g do not grow
+// with g; the search wants N_S - delta <= count(g) <= N_S.
 // A first trial at 1e-5 stands if it gives at most N_S.  Otherwise the
 // bracket (lo, hi) always has count(lo) > N_S, and hi is sqrt 3 or gives
 // fewer than N_S - delta; each further trial halves it.  A bracket narrower
 // than 1e-6 ends the search at hi, or at lo if the trial in hand gives no
 // supersegment; so does the 25th trial.
-template <typename Count>
-__host__ __device__ double search_gamma(int NS, int delta, Count count)
+// Counts come three at a time: a trial and the two that may follow it
+// (count3 fills a pass's counts, each right up to N_S and above it only known
+// to be above).  Sensitivities over `reach` (at least 2e-5, so that halving
+// towards the first trial ends), which no distance of the ray exceeds, give `runs`, the ray's runs of non-transparent samples, without a
+// pass; the first pass holds the first trial and the first two that need one.
+// The lanes of a wavefront take their passes together: each first settles
+// what its counts in hand decide.
+template <typename Count3>
+__host__ __device__ inline double search_gamma(int NS, int delta, int runs, double reach, Count3 count3)
 {
 #pragma clang fp contract(off)
-    double lo = 1e-5;
-    if (count(lo) <= NS) return lo;
-    double hi = sqrt(3.0);
-    int trials = 1;
+    double lo = 1e-5, hi = sqrt(3.0), g = lo;
+    double held[3];
+    int counts[3];
+    held[0] = lo;
+    double top = hi;
+    do {
+        held[1] = 0.5 * (lo + top);
+        top = held[1];
+    } while (held[1] > reach);
+    held[2] = 0.5 * (lo + held[1]);
+    int trials = 0;
     for (;;) {
-        const double g = 0.5 * (lo + hi);
-        const int c = count(g);
-        ++trials;
-        if (hi - lo < 1e-6) return c == 0 ? lo : hi;
-        if (c > NS)
-            lo = g;
-        else if (c < NS - delta)
-            hi = g;
-        else
-            return g;
-        if (trials == 25) return hi;
+        count3(held, counts);
+        for (;;) {
+            int c;
+            if (g > reach)
+                c = runs;
+            else if (g == held[0])
+                c = counts[0];
+            else if (g == held[1])
+                c = counts[1];
+            else if (g == held[2])
+                c = counts[2];
+            else
+                break;
+            ++trials;
+            if (trials == 1) {
+                if (c <= NS) return lo;
+            } else {
+                if (hi - lo < 1e-6) return c == 0 ? lo : hi;
+                if (c > NS)
+                    lo = g;
+                else if (c < NS - delta)
+                    hi = g;
+                else
+                    return g;
+                if (trials == 25) return hi;
+            }
+            g = 0.5 * (lo + hi);
+        }
+        held[0] = g;
+        held[1] = 0.5 * (lo + g);
+        held[2] = 0.5 * (g + hi);
     }
 }
 
@@ -312,24 +449,34 @@ __host__ __device__ inline void gen_ray(const GenParams &G, const SampleCache &C
     if (hit) {
         const int N = sample_count(G, t0, t1);
         const double len = (t1 - t0) / N;
-        // Direct volume rendering front to back: where early termination ends the ray.
-        double T = 1.0;
-        int ns = 0;
+        // Direct volume rendering front to back: where early termination ends
+        // the ray; and what bounds its distances (colours in [0, 1], and
+        // each normalised opacity, a mean, no more than the largest).
+        double T = 1.0, most = 0.0;
+        int ns = 0, runs = 0;
+        bool plain = true, gap = true;
         for (int q = 0; q < N; ++q) {
             const Sample s = take_sample(G, d, t0, len, q);
             if (q < C.K) C.p[(size_t)q * C.stride] = make_double2(s.v, s.a);
+            plain = plain && s.a <= 0.25 && (G.tf != VDI_TF_RAMP || (s.v >= 0.0 && s.v <= 1.0));
+            most = fmax(most, s.a);
+            runs += gap && s.a != 0.0 ? 1 : 0;
+            gap = s.a == 0.0;
             ++ns;
             T *= 1.0 - s.a;
             if (T <= kGenTTerm) break;
         }
+        const Passes P = {t0, len, ns, plain ? kFarErr : NAN};
         if (G.gamma > 0.0) {
             gamma = G.gamma;
         } else {
-            gamma = search_gamma(G.NS, G.delta, [&](double g) {
-                return split_ray<false>(G, C, d, cth, t0, len, ns, g, 0, li, plane, nullptr, nullptr);
+            const double reach = plain ? fmax(1.7322 * most, 2e-5) : INFINITY;
+            gamma = search_gamma(G.NS, G.delta, runs, reach, [&](const double *g, int *out) {
+                const Sensitivity s[3] = {sensitivity(g[0], P.err), sensitivity(g[1], P.err), sensitivity(g[2], P.err)};
+                count_segments<3>(G, C, d, P, s, G.NS, out);
             });
         }
-        n = split_ray<true>(G, C, d, cth, t0, len, ns, gamma, G.NS, li, plane, depth, rgba);
+        n = split_ray(G, C, d, cth, P, sensitivity(gamma, P.err), G.NS, li, plane, depth, rgba);
     }
     count[li] = (uint8_t)n;
     if (gamma_out) gamma_out[li] = gamma;
