@@ -896,45 +896,66 @@ struct SsimWeights {
     double w[2 * kSsimR + 1];             // 1-d Gaussian, normalised to sum 1
 };
 
+// A block scores a tile of kQualityTW x kQualityTH pixels.  The window is
+// separable: per channel, the five moments (x, y, xx, yy, xy) are summed along
+// the rows of the tile and of the 5 rows above and below it, from the pixels in
+// LDS into LDS, then along the columns: 11 + 11 weights a pixel instead of
+// 121, at 26 / 16 of the rows.  1280 x 720: 147 -> 57 us.
+constexpr int kQualityTW = 32, kQualityTH = 16;
+constexpr int kQualityLW = kQualityTW + 2 * kSsimR, kQualityLH = kQualityTH + 2 * kSsimR;
+
 // Per block: the sum of the SSIM (3 channels summed) of its valid pixels and
 // the sum of squared RGB differences of all its pixels, in a fixed order.
 __global__ __launch_bounds__(kQualityBlock) void k_quality_partials(const float4 *__restrict__ a,
                                                                     const float4 *__restrict__ b, int W, int H,
                                                                     SsimWeights g, double2 *__restrict__ part)
 {
+    __shared__ float pa[3][kQualityLH][kQualityLW], pb[3][kQualityLH][kQualityLW];
+    __shared__ double mom[5][kQualityLH][kQualityTW];
     __shared__ double sh[2][kQualityBlock];
-    const size_t n = (size_t)W * H;
-    const size_t i = (size_t)blockIdx.x * kQualityBlock + threadIdx.x;
+    const int tiles_x = (W + kQualityTW - 1) / kQualityTW;
+    const int x0 = (int)(blockIdx.x % (unsigned)tiles_x) * kQualityTW, y0 = (int)(blockIdx.x / (unsigned)tiles_x) * kQualityTH;
+    for (int i = threadIdx.x; i < kQualityLW * kQualityLH; i += kQualityBlock) {
+        // Pixels outside the image are in no window that counts.
+        const int lx = i % kQualityLW, ly = i / kQualityLW;
+        const int x = min(max(x0 + lx - kSsimR, 0), W - 1), y = min(max(y0 + ly - kSsimR, 0), H - 1);
+        const float4 u = a[(size_t)y * W + x], v = b[(size_t)y * W + x];
+        pa[0][ly][lx] = u.x, pa[1][ly][lx] = u.y, pa[2][ly][lx] = u.z;
+        pb[0][ly][lx] = v.x, pb[1][ly][lx] = v.y, pb[2][ly][lx] = v.z;
+    }
+    __syncthreads();
     double ssim = 0.0, se = 0.0;
-    if (i < n) {
-        const int x = (int)(i % W), y = (int)(i / W);
-        const float4 pa = a[i], pb = b[i];
-        const double d0 = (double)pa.x - pb.x, d1 = (double)pa.y - pb.y, d2 = (double)pa.z - pb.z;
-        se = d0 * d0 + d1 * d1 + d2 * d2;
-        if (x >= kSsimR && x < W - kSsimR && y >= kSsimR && y < H - kSsimR) {
-            double mx[3] = {0, 0, 0}, my[3] = {0, 0, 0}, sxx[3] = {0, 0, 0}, syy[3] = {0, 0, 0}, sxy[3] = {0, 0, 0};
-            for (int dy = -kSsimR; dy <= kSsimR; ++dy)
-                for (int dx = -kSsimR; dx <= kSsimR; ++dx) {
-                    const double w = g.w[dy + kSsimR] * g.w[dx + kSsimR];
-                    const size_t j = (size_t)(y + dy) * W + (x + dx);
-                    const float4 qa = a[j], qb = b[j];
-                    const double va[3] = {qa.x, qa.y, qa.z}, vb[3] = {qb.x, qb.y, qb.z};
-                    for (int c = 0; c < 3; ++c) {
-                        mx[c] += w * va[c];
-                        my[c] += w * vb[c];
-                        sxx[c] += w * va[c] * va[c];
-                        syy[c] += w * vb[c] * vb[c];
-                        sxy[c] += w * va[c] * vb[c];
-                    }
-                }
-            const double C1 = 0.01 * 0.01, C2 = 0.03 * 0.03;
-            for (int c = 0; c < 3; ++c) {
-                const double vx = sxx[c] - mx[c] * mx[c], vy = syy[c] - my[c] * my[c];
-                const double cxy = sxy[c] - mx[c] * my[c];
-                ssim += ((2 * mx[c] * my[c] + C1) * (2 * cxy + C2)) /
-                        ((mx[c] * mx[c] + my[c] * my[c] + C1) * (vx + vy + C2));
+    for (int c = 0; c < 3; ++c) {
+        for (int i = threadIdx.x; i < kQualityTW * kQualityLH; i += kQualityBlock) {
+            const int lx = i % kQualityTW, ly = i / kQualityTW;
+            double m[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k <= 2 * kSsimR; ++k) {
+                const double u = pa[c][ly][lx + k], v = pb[c][ly][lx + k], wu = g.w[k] * u, wv = g.w[k] * v;
+                m[0] += wu;
+                m[1] += wv;
+                m[2] = fma(wu, u, m[2]);
+                m[3] = fma(wv, v, m[3]);
+                m[4] = fma(wu, v, m[4]);
             }
+            for (int k = 0; k < 5; ++k) mom[k][ly][lx] = m[k];
         }
+        __syncthreads();
+        for (int i = threadIdx.x; i < kQualityTW * kQualityTH; i += kQualityBlock) {
+            const int lx = i % kQualityTW, ly = i / kQualityTW, x = x0 + lx, y = y0 + ly;
+            if (x >= W || y >= H) continue;
+            const double d = (double)pa[c][ly + kSsimR][lx + kSsimR] - pb[c][ly + kSsimR][lx + kSsimR];
+            se = fma(d, d, se);
+            if (x < kSsimR || x >= W - kSsimR || y < kSsimR || y >= H - kSsimR) continue;
+            double m[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k <= 2 * kSsimR; ++k)
+                for (int j = 0; j < 5; ++j) m[j] = fma(g.w[k], mom[j][ly + k][lx], m[j]);
+            const double C1 = 0.01 * 0.01, C2 = 0.03 * 0.03;
+            const double vx = m[2] - m[0] * m[0], vy = m[3] - m[1] * m[1], cxy = m[4] - m[0] * m[1];
+            ssim += ((2 * m[0] * m[1] + C1) * (2 * cxy + C2)) / ((m[0] * m[0] + m[1] * m[1] + C1) * (vx + vy + C2));
+        }
+        __syncthreads();
     }
     sh[0][threadIdx.x] = ssim;
     sh[1][threadIdx.x] = se;
@@ -1187,7 +1208,7 @@ extern "C" int vdi_image_quality(const float *image, const float *reference, int
     for (int k = -vdi::kSsimR; k <= vdi::kSsimR; ++k) sum += (g.w[k + vdi::kSsimR] = exp(-(k * k) / (2.0 * 1.5 * 1.5)));
     for (double &w : g.w) w /= sum;
     const size_t n = (size_t)width * height;
-    const int nparts = (int)((n + vdi::kQualityBlock - 1) / vdi::kQualityBlock);
+    const int nparts = ((width + vdi::kQualityTW - 1) / vdi::kQualityTW) * ((height + vdi::kQualityTH - 1) / vdi::kQualityTH);
     hipStream_t st = static_cast<hipStream_t>(stream);
     double2 *d_part = nullptr;
     hipError_t e = hipMallocAsync((void **)&d_part, (nparts + 1) * sizeof(double2), st);
