@@ -293,6 +293,49 @@ int validate_lists(const vdi_desc *d)
     return VDI_OK;
 }
 
+// Host-to-device copies of a VDI's arrays.  A copy from pageable host memory
+// waits for the device's other streams (measured: a create stalled behind a
+// server's running batch); copies from pinned memory are ordered on their
+// stream only.  Host arrays therefore go through two pinned halves of the
+// library, taken in turn: a half is refilled once the copy that last read it
+// has completed.  The halves are allocated on first use and kept.
+// A half's event is only asked while the stream it was recorded on is there:
+// before a VDI's stream goes, its copies are waited for and settled.
+constexpr size_t kPinHalf = (size_t)32 << 20;
+std::mutex g_pin_mu;
+void *g_pin[2] = {nullptr, nullptr};
+hipEvent_t g_pin_ev[2] = {nullptr, nullptr};
+hipStream_t g_pin_st[2] = {nullptr, nullptr};  // stream of the copy that may still read a half, or null
+
+// The work on `st` has been waited for.
+void settle_pins(hipStream_t st)
+{
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    for (int k = 0; k < 2; ++k)
+        if (g_pin_st[k] == st) g_pin_st[k] = nullptr;
+}
+
+hipError_t h2d(void *dst, const void *src, size_t n, hipStream_t st)
+{
+    std::lock_guard<std::mutex> lock(g_pin_mu);
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) {
+        if (!g_pin[k]) e = hipHostMalloc(&g_pin[k], kPinHalf, hipHostMallocDefault);
+        if (e == hipSuccess && !g_pin_ev[k]) e = hipEventCreateWithFlags(&g_pin_ev[k], hipEventDisableTiming);
+    }
+    static int k = 0;
+    for (size_t off = 0; off < n && e == hipSuccess; off += kPinHalf, k ^= 1) {
+        const size_t m = std::min(n - off, kPinHalf);
+        if (g_pin_st[k]) e = hipEventSynchronize(g_pin_ev[k]);
+        if (e != hipSuccess) break;
+        memcpy(g_pin[k], static_cast<const char *>(src) + off, m);
+        g_pin_st[k] = st;
+        e = hipMemcpyAsync(static_cast<char *>(dst) + off, g_pin[k], m, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = hipEventRecord(g_pin_ev[k], st);
+    }
+    return e;
+}
+
 void free_set(vdi::VdiSet &S)
 {
     // Errors are ignored: every pointer was allocated here or is null.
@@ -313,6 +356,7 @@ void free_vdi(vdi_s *v)
     free_set(v->back);
     if (v->stage) (void)hipFreeAsync(v->stage, v->copy);
     if (v->copy) (void)hipStreamSynchronize(v->copy);
+    if (v->copy) settle_pins(v->copy);
     for (int i = 0; i < vdi_s::kUseSlots; ++i)
         if (v->use_ev[i]) (void)hipEventDestroy(v->use_ev[i]);
     if (v->start) (void)hipEventDestroy(v->start);
@@ -321,24 +365,43 @@ void free_vdi(vdi_s *v)
     delete v;
 }
 
-// Checks of a descriptor common to vdi_create and vdi_replace_begin; on
-// success fills the V_O basis and the grid slice boundaries.
-// The count plane in host memory: d->count itself, or a copy of it in
-// `copy` when the planes are in device memory (they must be complete).
-int host_counts(const vdi_desc *d, std::vector<uint8_t> &copy, const uint8_t **out)
+// What the upload needs to know of the counts: their sum, and that none
+// exceeds max_supersegments.  A host plane is read here; a device plane by a
+// kernel on `st`, whose few results are waited for (the plane must be complete).
+int check_counts(const vdi_desc *d, hipStream_t st, uint64_t *total)
 {
+    const uint64_t plane = (uint64_t)d->width * d->height;
+    uint64_t sum = 0;
+    uint32_t most = 0;
     if (!d->planes_on_device) {
-        *out = d->count;
-        return VDI_OK;
+        for (uint64_t li = 0; li < plane; ++li) {
+            sum += d->count[li];
+            most = std::max<uint32_t>(most, d->count[li]);
+        }
+    } else {
+        vdi::CountStats part[vdi::kCountBlocks], *d_part = nullptr;
+        hipError_t e = hipMallocAsync((void **)&d_part, sizeof part, st);
+        if (e != hipSuccess) return hip_fail(e, "count statistics");
+        e = vdi::launch_count_stats(d->count, plane, d_part, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(part, d_part, sizeof part, hipMemcpyDeviceToHost, st);
+        const hipError_t ef = hipFreeAsync(d_part, st), es = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = ef;
+        if (e == hipSuccess) e = es;
+        if (e != hipSuccess) return hip_fail(e, "count plane download");
+        for (const vdi::CountStats &p : part) {
+            sum += p.sum;
+            most = std::max(most, p.most);
+        }
     }
-    copy.resize((size_t)d->width * d->height);
-    const hipError_t e = hipMemcpy(copy.data(), d->count, copy.size(), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(e, "count plane download");
-    *out = copy.data();
+    if (most > (uint32_t)d->max_supersegments) return fail(VDI_ERR_ARG, "a list count exceeds max_supersegments");
+    *total = sum;
     return VDI_OK;
 }
 
-int check_desc(const vdi_desc *d, Basis &ob, std::vector<float> &gz, const uint8_t **counts, std::vector<uint8_t> &count_copy)
+// Checks of a descriptor common to vdi_create and vdi_replace_begin, the counts
+// of device planes left to check_counts; on success fills the V_O basis and the
+// grid slice boundaries.
+int check_desc(const vdi_desc *d, Basis &ob, std::vector<float> &gz, uint64_t *total)
 {
     if (d->width < 1 || d->height < 1 || d->width > 32768 || d->height > 32768)
         return fail(VDI_ERR_ARG, "VDI size %dx%d out of range", d->width, d->height);
@@ -364,11 +427,10 @@ int check_desc(const vdi_desc *d, Basis &ob, std::vector<float> &gz, const uint8
     if (d->planes_on_device != 0 && d->planes_on_device != 1) return fail(VDI_ERR_ARG, "planes_on_device must be 0 or 1");
     if (d->planes_on_device && d->validate)
         return fail(VDI_ERR_ARG, "list validation reads the planes on the host: not available for device planes");
-    rc = host_counts(d, count_copy, counts);
-    if (rc) return rc;
-    const uint64_t plane = (uint64_t)d->width * d->height;
-    for (uint64_t li = 0; li < plane; ++li)
-        if ((*counts)[li] > d->max_supersegments) return fail(VDI_ERR_ARG, "a list count exceeds max_supersegments");
+    if (!d->planes_on_device) {
+        rc = check_counts(d, nullptr, total);
+        if (rc) return rc;
+    }
     if (d->validate) {
         rc = validate_lists(d);
         if (rc) return rc;
@@ -408,51 +470,13 @@ uint64_t set_bytes_of(const vdi_desc *d)
            (cells + 31) / 32 * sizeof(uint32_t) + (uint64_t)(d->grid_nz + 1) * sizeof(float);
 }
 
-// Host-to-device copies of a VDI's arrays.  A copy from pageable host memory
-// waits for the device's other streams (measured: a create stalled behind a
-// server's running batch); copies from pinned memory are ordered on their
-// stream only.  Host arrays therefore go through two pinned halves of the
-// library, taken in turn: a half is refilled once the copy that last read it
-// has completed.  The halves are allocated on first use and kept.
-constexpr size_t kPinHalf = (size_t)32 << 20;
-std::mutex g_pin_mu;
-void *g_pin[2] = {nullptr, nullptr};
-hipEvent_t g_pin_ev[2] = {nullptr, nullptr};
-
-hipError_t h2d(void *dst, const void *src, size_t n, hipStream_t st)
-{
-    std::lock_guard<std::mutex> lock(g_pin_mu);
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-        if (!g_pin[k]) e = hipHostMalloc(&g_pin[k], kPinHalf, hipHostMallocDefault);
-        if (e == hipSuccess && !g_pin_ev[k]) e = hipEventCreateWithFlags(&g_pin_ev[k], hipEventDisableTiming);
-    }
-    static int k = 0;
-    for (size_t off = 0; off < n && e == hipSuccess; off += kPinHalf, k ^= 1) {
-        const size_t m = std::min(n - off, kPinHalf);
-        e = hipEventSynchronize(g_pin_ev[k]);
-        if (e != hipSuccess) break;
-        memcpy(g_pin[k], static_cast<const char *>(src) + off, m);
-        e = hipMemcpyAsync(static_cast<char *>(dst) + off, g_pin[k], m, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipEventRecord(g_pin_ev[k], st);
-    }
-    return e;
-}
-
-// A copy of a VDI array: device to device when the planes are on the device.
-hipError_t copy_in(void *dst, const void *src, size_t n, bool on_device, hipStream_t st)
-{
-    if (on_device) return hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToDevice, st);
-    return h2d(dst, src, n, st);
-}
-
 // Upload d into the set S on stream st: allocate S's buffers if it has none,
-// copy the count plane and slice boundaries, stage whole slot planes through
-// `stage` (stage_bytes) and scatter them into storage order (colour
-// converted on the way), then build the count grid.  Enqueues only; the
-// caller synchronises.  `gz` must stay valid until the work has run.
-hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, const uint8_t *counts, const Basis &ob,
-                      const std::vector<float> &gz, hipStream_t st, void *stage, uint64_t stage_bytes, const char **what)
+// copy the count plane and slice boundaries and scatter the slot planes into
+// storage order (colour converted on the way): device planes from where they
+// are, host planes as many whole slots at a time as `stage` (stage_bytes)
+// holds; then build the count grid.  Enqueues only; the caller synchronises.
+hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, uint64_t total, const Basis &ob, const std::vector<float> &gz,
+                      hipStream_t st, void *stage, uint64_t stage_bytes, const char **what)
 {
     const uint64_t plane = (uint64_t)d->width * d->height;
     const uint64_t ns = (uint64_t)d->max_supersegments;
@@ -498,29 +522,28 @@ hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, const uint8_t *counts, 
     D.gz = S.d_gz;
     *what = "upload";
     const bool on_dev = d->planes_on_device != 0;
-    e = copy_in(S.d_count, d->count, plane, on_dev, st);
-    if (e == hipSuccess) e = h2d(S.d_gz, gz.data(), gz.size() * sizeof(float), st);
+    e = on_dev ? hipMemcpyAsync(S.d_count, d->count, plane, hipMemcpyDeviceToDevice, st) : h2d(S.d_count, d->count, plane, st);
+    if (e == hipSuccess) e = vdi::launch_set_gz(gz.data(), (int32_t)gz.size(), S.d_gz, st);
     const size_t colour_in = d->rgba_fmt_in == VDI_F32 ? 16 : 8;
-    const uint64_t slots = std::max<uint64_t>(1, std::min<uint64_t>(ns, stage_bytes / (plane * 16)));
+    const uint64_t slots = on_dev ? ns : std::max<uint64_t>(1, std::min<uint64_t>(ns, stage_bytes / (plane * 16)));
     for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
         const bool dep = pass == 0;
         const size_t esz = dep ? sizeof(float2) : colour_in;
         const char *src = static_cast<const char *>(dep ? (const void *)d->depth : d->rgba);
         for (uint64_t j0 = 0; j0 < ns && e == hipSuccess; j0 += slots) {
             const uint64_t nj = std::min(slots, ns - j0);
+            const char *from = src + j0 * plane * esz;
             // Stream order keeps the staging buffer from being refilled before it is scattered.
-            e = copy_in(stage, src + j0 * plane * esz, nj * plane * esz, on_dev, st);
+            if (!on_dev) e = h2d(stage, from, nj * plane * esz, st);
             if (e == hipSuccess)
-                e = vdi::launch_scatter_slots(stage, d->rgba_fmt_in, dep ? (void *)S.d_depth : S.d_rgba, d->rgba_fmt_store,
-                                              dep, nj * plane, D, (int32_t)j0, st);
+                e = vdi::launch_scatter_slots(on_dev ? from : stage, d->rgba_fmt_in, dep ? (void *)S.d_depth : S.d_rgba,
+                                              d->rgba_fmt_store, dep, (int32_t)j0, (int32_t)nj, D, st);
         }
     }
     if (e != hipSuccess) return e;
     *what = "grid build";
     e = vdi::launch_grid_build(D, S.d_grid, st);
     if (e == hipSuccess) e = vdi::launch_grid_bits(D, S.d_gbits, st);
-    uint64_t total = 0;
-    for (uint64_t li = 0; li < plane; ++li) total += counts[li];
     S.supersegments = total;
     return e;
 }
@@ -661,9 +684,8 @@ int vdi_create(const vdi_desc *d, vdi_t *out)
     if (!d || !out) return fail(VDI_ERR_ARG, "null argument");
     Basis ob;
     std::vector<float> gz;
-    std::vector<uint8_t> count_copy;
-    const uint8_t *counts = nullptr;
-    int rc = check_desc(d, ob, gz, &counts, count_copy);
+    uint64_t total = 0;
+    int rc = check_desc(d, ob, gz, &total);
     if (rc) return rc;
     vdi_s *v = new (std::nothrow) vdi_s();
     if (!v) return fail(VDI_ERR_OOM, "host allocation");
@@ -686,8 +708,15 @@ int vdi_create(const vdi_desc *d, vdi_t *out)
     // waited for the device's other work as well (measured).
     if (e == hipSuccess) what = "VDI stream", e = hipStreamCreateWithFlags(&v->copy, hipStreamNonBlocking);
     hipStream_t st = v->copy;
-    if (e == hipSuccess) what = "staging", e = hipMallocAsync(&stage, stage_bytes, st);
-    if (e == hipSuccess) e = upload_set(v->cur, d, counts, ob, gz, st, stage, stage_bytes, &what);
+    if (e == hipSuccess && d->planes_on_device) {
+        rc = check_counts(d, st, &total);
+        if (rc) {
+            free_vdi(v);
+            return rc;
+        }
+    }
+    if (e == hipSuccess && !d->planes_on_device) what = "staging", e = hipMallocAsync(&stage, stage_bytes, st);
+    if (e == hipSuccess) e = upload_set(v->cur, d, total, ob, gz, st, stage, stage_bytes, &what);
     if (stage) {
         const hipError_t ef = hipFreeAsync(stage, st);
         if (e == hipSuccess) e = ef;
@@ -718,9 +747,8 @@ int vdi_replace_begin(vdi_t v, const vdi_desc *d, void *stream)
     }
     Basis ob;
     std::vector<float> gz;
-    std::vector<uint8_t> count_copy;
-    const uint8_t *counts = nullptr;
-    int rc = check_desc(d, ob, gz, &counts, count_copy);
+    uint64_t total = 0;
+    int rc = check_desc(d, ob, gz, &total);
     if (rc) return rc;
     {
         std::lock_guard<std::mutex> lock(v->mu);
@@ -731,25 +759,30 @@ int vdi_replace_begin(vdi_t v, const vdi_desc *d, void *stream)
         if (v->pending) return fail(VDI_ERR_STATE, "a replacement is already pending");
         v->pending = true;
         v->enqueued = false;
-        v->gz_host = gz;
     }
     // From here only this call touches the back set and the copy stream.
     const uint64_t plane = (uint64_t)d->width * d->height;
     const char *what = "replacement set-up";
     hipError_t e = hipSetDevice(v->device);
-    if (e == hipSuccess && !v->start) {
-        e = hipEventCreateWithFlags(&v->start, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ready, hipEventDisableTiming);
-        if (e == hipSuccess) {
-            v->stage_bytes = std::max<uint64_t>(256ull << 20, plane * 16);
-            e = hipMallocAsync(&v->stage, v->stage_bytes, v->copy);
+    if (e == hipSuccess && d->planes_on_device) {
+        rc = check_counts(d, v->copy, &total);
+        if (rc) {
+            std::lock_guard<std::mutex> lock(v->mu);
+            v->pending = false;
+            return rc;
         }
+    }
+    if (e == hipSuccess && !v->start) e = hipEventCreateWithFlags(&v->start, hipEventDisableTiming);
+    if (e == hipSuccess && !v->ready) e = hipEventCreateWithFlags(&v->ready, hipEventDisableTiming);
+    if (e == hipSuccess && !v->stage && !d->planes_on_device) {
+        v->stage_bytes = std::max<uint64_t>(256ull << 20, plane * 16);
+        e = hipMallocAsync(&v->stage, v->stage_bytes, v->copy);
     }
     // The back set may be the one renders used before the last swap: the
     // upload waits for the work already enqueued on the caller's stream.
     if (e == hipSuccess) e = hipEventRecord(v->start, static_cast<hipStream_t>(stream));
     if (e == hipSuccess) e = hipStreamWaitEvent(v->copy, v->start, 0);
-    if (e == hipSuccess) e = upload_set(v->back, d, counts, ob, v->gz_host, v->copy, v->stage, v->stage_bytes, &what);
+    if (e == hipSuccess) e = upload_set(v->back, d, total, ob, gz, v->copy, v->stage, v->stage_bytes, &what);
     if (e == hipSuccess) what = "replacement", e = hipEventRecord(v->ready, v->copy);
     std::lock_guard<std::mutex> lock(v->mu);
     if (e != hipSuccess) {

@@ -243,7 +243,6 @@ struct vdi_s {
     uint64_t stage_bytes = 0;
     bool pending = false;            // a replacement was started and not yet swapped in
     bool enqueued = false;           // ... and all of its work is on the copy stream
-    std::vector<float> gz_host;      // slice boundaries of the pending upload
     // Renders in flight, for vdi_destroy: an event recorded after the last
     // render of v on each of up to kUseSlots streams (created with v, so a
     // render allocates nothing), and the requests a server holds on v.
@@ -302,10 +301,20 @@ hipError_t launch_upsample(const float4 *lo, int32_t w, int32_t h, float4 *out, 
 hipError_t launch_grid_build(const DevVDI &v, uint32_t *grid, hipStream_t stream);
 // Occupancy bits of the count grid (see DevVDI::gbits).
 hipError_t launch_grid_bits(const DevVDI &v, uint32_t *bits, hipStream_t stream);
-// n elements of slot-major input planes, starting at slot j0 (n a multiple of
-// v.plane), into v's storage order; colour converted from fmt_in to fmt_store.
-hipError_t launch_scatter_slots(const void *src, int32_t fmt_in, void *dst, int32_t fmt_store, bool depth, uint64_t n,
-                                const DevVDI &v, int32_t j0, hipStream_t stream);
+// Slots [j0, j0 + nj) of slot-major input planes (src: slot j0) into v's
+// storage order, as far as v.count, which must be set on `stream` before, says
+// that a list has them; colour converted from fmt_in to fmt_store.
+hipError_t launch_scatter_slots(const void *src, int32_t fmt_in, void *dst, int32_t fmt_store, bool depth, int32_t j0,
+                                int32_t nj, const DevVDI &v, hipStream_t stream);
+// Largest value and sum of a count plane in device memory, in kCountBlocks parts.
+struct CountStats {
+    uint64_t sum;
+    uint32_t most, pad;
+};
+constexpr int kCountBlocks = 256;
+hipError_t launch_count_stats(const uint8_t *count, uint64_t n, CountStats *out, hipStream_t stream);
+// n <= VDI_MAX_GRID_NZ + 1 slice boundaries into device memory, by value.
+hipError_t launch_set_gz(const float *z, int32_t n, float *gz, hipStream_t stream);
 // Batched launches: `jobs` is a device array of njobs records sorted by
 // tile0, all of colour format fmt; nblocks covers the last job's tiles.
 // Exact jobs use the window search with empty-space skipping.
