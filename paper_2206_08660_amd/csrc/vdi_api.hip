@@ -121,6 +121,10 @@ int build_frame(const vdi::VdiSet &S, const vdi_camera &cam, int w, int h, doubl
     f.tx_n = n.th * aspect;
     f.ty_n = n.th;
     f.near_n = cam.near_plane;
+    f.inv_wo = 1.0f / (float)S.dev.WO;
+    f.inv_ho = 1.0f / (float)S.dev.HO;
+    f.inv_w = 1.0 / w;
+    f.inv_h = 1.0 / h;
     f.W = w;
     f.H = h;
     f.ess = 1;

@@ -92,13 +92,15 @@ static_assert(kBrick == 0 || (kBrick & (kBrick - 1)) == 0, "bricks must hold a p
 constexpr int kBrickW = kBrick == 0 ? 1 : VDI_BRICK_W;
 constexpr int kBrickH = kBrick == 0 ? 1 : kBrick / kBrickW;
 
-// Storage offset of slot 0 of list (ix, iy) of a WO-wide list grid.
-__host__ __device__ inline uint64_t list_base_xy(int ix, int iy, int NS, int WO)
+// Storage offset of slot 0 of list (ix, iy) of a WO-wide list grid.  Idx: see
+// fits32.
+template <typename Idx = uint64_t>
+__host__ __device__ inline Idx list_base_xy(int ix, int iy, int NS, int WO)
 {
-    if constexpr (kBrick == 0) return (uint64_t)iy * WO + ix;
+    if constexpr (kBrick == 0) return (Idx)iy * (Idx)WO + (Idx)ix;
     const uint32_t bw = (uint32_t)(WO + kBrickW - 1) / kBrickW;
-    const uint64_t brick = (uint64_t)((uint32_t)iy / kBrickH) * bw + (uint32_t)ix / kBrickW;
-    return brick * ((uint64_t)NS * kBrick) + ((uint32_t)iy % kBrickH) * kBrickW + (uint32_t)ix % kBrickW;
+    const Idx brick = (Idx)((uint32_t)iy / kBrickH) * bw + (uint32_t)ix / kBrickW;
+    return brick * ((Idx)NS * kBrick) + ((uint32_t)iy % kBrickH) * kBrickW + (uint32_t)ix % kBrickW;
 }
 __host__ __device__ inline uint64_t list_base(uint64_t li, int NS, int WO)
 {
@@ -110,6 +112,14 @@ __host__ __device__ inline uint64_t plane_elems(int WO, int HO, int NS)
     if constexpr (kBrick == 0) return (uint64_t)WO * HO * (uint64_t)NS;
     return (uint64_t)((WO + kBrickW - 1) / kBrickW) * ((HO + kBrickH - 1) / kBrickH) * kBrick * (uint64_t)NS;
 }
+
+// Whether byte offsets into every plane of a VDI fit 32 bits (colours, 16
+// bytes a slot, are the largest): the kernels then add 32-bit offsets to a
+// scalar base, where 64-bit offsets take a multi-cycle multiply, two
+// instructions for each address and two registers.  Of the workloads here all
+// fit (1920 x 1080 / N_S 50: 1.7 GB); those that do not run the same code with
+// 64-bit offsets.
+__host__ __device__ inline bool fits32(int WO, int HO, int NS) { return plane_elems(WO, HO, NS) <= 0xffffffffull / 16; }
 
 // A resident VDI as the kernels see it.
 struct DevVDI {
@@ -140,6 +150,8 @@ struct Frame {
     double eyeN[3], FN[3], RN[3], UN[3];
     double tx_n, ty_n, near_n;
     double bmin[3], bmax[3];
+    float inv_wo, inv_ho;      // 1 / WO, 1 / HO (list_cos)
+    double inv_w, inv_h;       // 1 / W, 1 / H
     int32_t W, H;              // rays cast
     int32_t ess, search;
     double DR;                 // > 0: along-ray subsampling
@@ -317,9 +329,10 @@ hipError_t launch_count_stats(const uint8_t *count, uint64_t n, CountStats *out,
 hipError_t launch_set_gz(const float *z, int32_t n, float *gz, hipStream_t stream);
 // Batched launches: `jobs` is a device array of njobs records sorted by
 // tile0, all of colour format fmt; nblocks covers the last job's tiles.
-// Exact jobs use the window search with empty-space skipping.
+// Exact jobs use the window search with empty-space skipping.  wide: some
+// job's VDI does not fit 32-bit offsets (fits32).
 hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, bool preview,
-                               hipStream_t stream);
+                               bool wide, hipStream_t stream);
 hipError_t launch_batch_upsample(const UpsampleJob *jobs, int32_t njobs, uint32_t nblocks, hipStream_t stream);
 // Persistent served launch of `blocks` workgroups (see PHost, PQueue; jobs
 // gets the records of host_jobs), for VDIs whose colour is stored in format

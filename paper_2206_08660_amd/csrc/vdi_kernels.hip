@@ -40,7 +40,7 @@ namespace {
 #endif
 #define VDI_EXACT_OCC __attribute__((amdgpu_waves_per_eu(VDI_EXACT_WAVES)))
 
-template <int FMT, int SEARCH, bool ESS, bool COUNT>
+template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx>
 __global__ __launch_bounds__(kBlock) VDI_EXACT_OCC void k_render_exact(DevVDI V, Frame F)
 {
     __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kBlock) VDI_EXACT_OCC void k_render_exact(DevVDI V,
     const int py = (tile / tiles_x) * kXTileH + (threadIdx.x / kXTileW);
     if (px >= F.W || py >= F.H) return;
     Counters cnt = {0, 0};
-    F.out[(uint64_t)py * F.W + px] = trace_exact<FMT, SEARCH, ESS, COUNT>(V, F, s_gz, px, py, cnt);
+    F.out[(uint64_t)py * F.W + px] = trace_exact<FMT, SEARCH, ESS, COUNT, Idx>(V, F, s_gz, px, py, cnt);
     if constexpr (COUNT) {
         if (F.ray_stats) {
             F.ray_stats[2 * ((uint64_t)py * F.W + px)] = cnt.lists;
@@ -84,7 +84,7 @@ __device__ __forceinline__ void store_px(float4 *p, float4 v)
 // One preview tile (preview_tile_dims): tw x th rays, F.parts adjacent lanes
 // per ray.  Lanes outside the image take part in the combination with an
 // empty result.
-template <int FMT, bool COUNT = false, bool WT = false>
+template <int FMT, typename Idx, bool COUNT = false, bool WT = false>
 __device__ __forceinline__ void preview_tile(const DevVDI &V, const Frame &F, const float *s_gz, int tile_index)
 {
     const int parts = F.parts;
@@ -98,7 +98,7 @@ __device__ __forceinline__ void preview_tile(const DevVDI &V, const Frame &F, co
     const bool in = px < F.W && py < F.H;
     Accum a = {0.0f, 0.0f, 0.0f, 1.0f};
     Counters cnt = {0, 0};
-    if (in) a = trace_preview<FMT, COUNT>(V, F, s_gz, px, py, lane % parts, parts, &cnt);
+    if (in) a = trace_preview<FMT, COUNT, Idx>(V, F, s_gz, px, py, lane % parts, parts, &cnt);
     a = combine_parts(a, parts, lane);
     if (in && lane % parts == 0) store_px<WT>(&F.out[(uint64_t)py * F.W + px], to_rgba(a));
     if constexpr (COUNT) {
@@ -109,13 +109,13 @@ __device__ __forceinline__ void preview_tile(const DevVDI &V, const Frame &F, co
     }
 }
 
-template <int FMT, bool COUNT>
+template <int FMT, bool COUNT, typename Idx>
 __global__ __launch_bounds__(kBlock) void k_render_preview(DevVDI V, Frame F)
 {
     __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
     for (int i = threadIdx.x; i <= V.gnz; i += kBlock) s_gz[i] = V.gz[i];
     __syncthreads();
-    preview_tile<FMT, COUNT>(V, F, s_gz, blockIdx.x);
+    preview_tile<FMT, Idx, COUNT>(V, F, s_gz, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -136,7 +136,7 @@ __device__ __forceinline__ const J &job_of(const J *__restrict__ jobs, int njobs
     return jobs[lo];
 }
 
-template <int FMT, bool PREVIEW>
+template <int FMT, bool PREVIEW, typename Idx>
 __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, int njobs)
 {
     __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
@@ -146,7 +146,7 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
     for (int i = threadIdx.x; i <= J.V.gnz; i += kBlock) s_gz[i] = J.V.gz[i];
     __syncthreads();
     if constexpr (PREVIEW) {
-        preview_tile<FMT>(J.V, J.F, s_gz, (int)local);
+        preview_tile<FMT, Idx>(J.V, J.F, s_gz, (int)local);
     } else {
         const int tiles_x = (J.F.W + kXTileW - 1) / kXTileW, tiles_y = (J.F.H + kXTileH - 1) / kXTileH;
         const int tile = xcd_tile((int)local, tiles_x, tiles_y, kXBandRows);
@@ -154,7 +154,7 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
         const int py = (tile / tiles_x) * kXTileH + (threadIdx.x / kXTileW);
         if (px >= J.F.W || py >= J.F.H) return;
         Counters cnt = {0, 0};
-        J.F.out[(uint64_t)py * J.F.W + px] = trace_exact<FMT, VDI_SEARCH_WINDOW, true, false>(J.V, J.F, s_gz, px, py, cnt);
+        J.F.out[(uint64_t)py * J.F.W + px] = trace_exact<FMT, VDI_SEARCH_WINDOW, true, false, Idx>(J.V, J.F, s_gz, px, py, cnt);
     }
 }
 
@@ -162,15 +162,15 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
 // preview tiles at the preview kernel's (its registers, 5 wavefronts): held
 // to 80 VGPRs the preview loop spilled, and the benchmark step took
 // 9.95-10.09 ms against 9.74-9.83 ms.
-template <int FMT>
+template <int FMT, typename Idx>
 __global__ __launch_bounds__(kBlock) VDI_EXACT_OCC void k_render_batch(const BatchJob *__restrict__ jobs, int njobs)
 {
-    batch_tile<FMT, false>(jobs, njobs);
+    batch_tile<FMT, false, Idx>(jobs, njobs);
 }
-template <int FMT>
+template <int FMT, typename Idx>
 __global__ __launch_bounds__(kBlock) void k_render_batch_preview(const BatchJob *__restrict__ jobs, int njobs)
 {
-    batch_tile<FMT, true>(jobs, njobs);
+    batch_tile<FMT, true, Idx>(jobs, njobs);
 }
 
 __global__ __launch_bounds__(256) void k_upsample_batch(const UpsampleJob *__restrict__ jobs, int njobs)
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(kBlock) VDI_PERSIST_OCC void k_persist(const PHost 
             for (int i = lane; i <= J.R.V.gnz; i += kBlock) s_gz[i] = J.R.V.gz[i];
             __syncthreads();
             if (J.preview) {
-                preview_tile<FMT, false, true>(J.R.V, J.R.F, s_gz, (int)local);
+                preview_tile<FMT, uint64_t, false, true>(J.R.V, J.R.F, s_gz, (int)local);
             } else {
                 const int tiles_x = (J.R.F.W + kXTileW - 1) / kXTileW, tiles_y = (J.R.F.H + kXTileH - 1) / kXTileH;
                 const int tile = xcd_tile((int)local, tiles_x, tiles_y, kXBandRows);
@@ -574,27 +574,38 @@ __global__ void k_set_gz(SliceBounds b, int n, float *__restrict__ gz)
         if (i < n && (int)threadIdx.x == i) gz[i] = b.z[i];
 }
 
-template <int FMT, bool COUNT>
+template <int FMT, bool COUNT, typename Idx>
 hipError_t launch_exact_fmt(const DevVDI &v, const Frame &f, dim3 grid, hipStream_t s)
 {
     const bool ess = f.ess != 0;
+    auto k = k_render_exact<FMT, VDI_SEARCH_SEEDED, true, COUNT, Idx>;
     switch (f.search) {
     case VDI_SEARCH_BINARY:
-        if (ess) k_render_exact<FMT, VDI_SEARCH_BINARY, true, COUNT><<<grid, kBlock, 0, s>>>(v, f);
-        else k_render_exact<FMT, VDI_SEARCH_BINARY, false, COUNT><<<grid, kBlock, 0, s>>>(v, f);
+        k = ess ? k_render_exact<FMT, VDI_SEARCH_BINARY, true, COUNT, Idx> : k_render_exact<FMT, VDI_SEARCH_BINARY, false, COUNT, Idx>;
         break;
     case VDI_SEARCH_LINEAR:
-        if (ess) k_render_exact<FMT, VDI_SEARCH_LINEAR, true, COUNT><<<grid, kBlock, 0, s>>>(v, f);
-        else k_render_exact<FMT, VDI_SEARCH_LINEAR, false, COUNT><<<grid, kBlock, 0, s>>>(v, f);
+        k = ess ? k_render_exact<FMT, VDI_SEARCH_LINEAR, true, COUNT, Idx> : k_render_exact<FMT, VDI_SEARCH_LINEAR, false, COUNT, Idx>;
         break;
     case VDI_SEARCH_WINDOW:
-        if (ess) k_render_exact<FMT, VDI_SEARCH_WINDOW, true, COUNT><<<grid, kBlock, 0, s>>>(v, f);
-        else k_render_exact<FMT, VDI_SEARCH_WINDOW, false, COUNT><<<grid, kBlock, 0, s>>>(v, f);
+        k = ess ? k_render_exact<FMT, VDI_SEARCH_WINDOW, true, COUNT, Idx> : k_render_exact<FMT, VDI_SEARCH_WINDOW, false, COUNT, Idx>;
         break;
     default:
-        if (ess) k_render_exact<FMT, VDI_SEARCH_SEEDED, true, COUNT><<<grid, kBlock, 0, s>>>(v, f);
-        else k_render_exact<FMT, VDI_SEARCH_SEEDED, false, COUNT><<<grid, kBlock, 0, s>>>(v, f);
+        if (!ess) k = k_render_exact<FMT, VDI_SEARCH_SEEDED, false, COUNT, Idx>;
     }
+    k<<<grid, kBlock, 0, s>>>(v, f);
+    return hipGetLastError();
+}
+
+// The default options with 32-bit offsets where they fit; the other searches,
+// the counters and larger VDIs with 64-bit ones.
+template <int FMT>
+hipError_t launch_exact_of(const DevVDI &v, const Frame &f, bool counters, dim3 grid, hipStream_t s)
+{
+    if (counters) return launch_exact_fmt<FMT, true, uint64_t>(v, f, grid, s);
+    if (f.search != VDI_SEARCH_WINDOW || !fits32(v.WO, v.HO, v.NS)) return launch_exact_fmt<FMT, false, uint64_t>(v, f, grid, s);
+    auto k = f.ess ? k_render_exact<FMT, VDI_SEARCH_WINDOW, true, false, uint32_t>
+                   : k_render_exact<FMT, VDI_SEARCH_WINDOW, false, false, uint32_t>;
+    k<<<grid, kBlock, 0, s>>>(v, f);
     return hipGetLastError();
 }
 
@@ -608,38 +619,31 @@ inline dim3 tile_grid(int W, int H)
 hipError_t launch_render_exact(const DevVDI &v, const Frame &f, bool counters, hipStream_t s)
 {
     const dim3 g = tile_grid(f.W, f.H);
-    if (counters) {
-        switch (v.fmt) {
-        case VDI_F16: return launch_exact_fmt<VDI_F16, true>(v, f, g, s);
-        case VDI_BF16: return launch_exact_fmt<VDI_BF16, true>(v, f, g, s);
-        default: return launch_exact_fmt<VDI_F32, true>(v, f, g, s);
-        }
-    }
     switch (v.fmt) {
-    case VDI_F16: return launch_exact_fmt<VDI_F16, false>(v, f, g, s);
-    case VDI_BF16: return launch_exact_fmt<VDI_BF16, false>(v, f, g, s);
-    default: return launch_exact_fmt<VDI_F32, false>(v, f, g, s);
+    case VDI_F16: return launch_exact_of<VDI_F16>(v, f, counters, g, s);
+    case VDI_BF16: return launch_exact_of<VDI_BF16>(v, f, counters, g, s);
+    default: return launch_exact_of<VDI_F32>(v, f, counters, g, s);
     }
+}
+
+template <int FMT>
+hipError_t launch_preview_of(const DevVDI &v, const Frame &f, bool counters, dim3 grid, hipStream_t s)
+{
+    auto k = counters ? k_render_preview<FMT, true, uint64_t>
+                      : (fits32(v.WO, v.HO, v.NS) ? k_render_preview<FMT, false, uint32_t> : k_render_preview<FMT, false, uint64_t>);
+    k<<<grid, kBlock, 0, s>>>(v, f);
+    return hipGetLastError();
 }
 
 hipError_t launch_render_preview(const DevVDI &v, const Frame &f, bool counters, hipStream_t s)
 {
     if (f.parts != preview_parts(f.W, f.H)) return hipErrorInvalidValue;
     const dim3 g(preview_tiles(f.W, f.H));
-    if (counters) {
-        switch (v.fmt) {
-        case VDI_F16: k_render_preview<VDI_F16, true><<<g, kBlock, 0, s>>>(v, f); break;
-        case VDI_BF16: k_render_preview<VDI_BF16, true><<<g, kBlock, 0, s>>>(v, f); break;
-        default: k_render_preview<VDI_F32, true><<<g, kBlock, 0, s>>>(v, f); break;
-        }
-        return hipGetLastError();
-    }
     switch (v.fmt) {
-    case VDI_F16: k_render_preview<VDI_F16, false><<<g, kBlock, 0, s>>>(v, f); break;
-    case VDI_BF16: k_render_preview<VDI_BF16, false><<<g, kBlock, 0, s>>>(v, f); break;
-    default: k_render_preview<VDI_F32, false><<<g, kBlock, 0, s>>>(v, f); break;
+    case VDI_F16: return launch_preview_of<VDI_F16>(v, f, counters, g, s);
+    case VDI_BF16: return launch_preview_of<VDI_BF16>(v, f, counters, g, s);
+    default: return launch_preview_of<VDI_F32>(v, f, counters, g, s);
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_upsample(const float4 *lo, int32_t w, int32_t h, float4 *out, int32_t W, int32_t H, hipStream_t s)
@@ -649,24 +653,24 @@ hipError_t launch_upsample(const float4 *lo, int32_t w, int32_t h, float4 *out, 
     return hipGetLastError();
 }
 
-hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, bool preview,
+template <int FMT>
+hipError_t launch_batch_of(const BatchJob *jobs, int32_t njobs, dim3 grid, bool preview, bool wide, hipStream_t s)
+{
+    auto k = wide ? (preview ? k_render_batch_preview<FMT, uint64_t> : k_render_batch<FMT, uint64_t>)
+                  : (preview ? k_render_batch_preview<FMT, uint32_t> : k_render_batch<FMT, uint32_t>);
+    k<<<grid, kBlock, 0, s>>>(jobs, njobs);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, bool preview, bool wide,
                                hipStream_t s)
 {
     const dim3 g(nblocks);
-    if (preview) {
-        switch (fmt) {
-        case VDI_F16: k_render_batch_preview<VDI_F16><<<g, kBlock, 0, s>>>(jobs, njobs); break;
-        case VDI_BF16: k_render_batch_preview<VDI_BF16><<<g, kBlock, 0, s>>>(jobs, njobs); break;
-        default: k_render_batch_preview<VDI_F32><<<g, kBlock, 0, s>>>(jobs, njobs); break;
-        }
-    } else {
-        switch (fmt) {
-        case VDI_F16: k_render_batch<VDI_F16><<<g, kBlock, 0, s>>>(jobs, njobs); break;
-        case VDI_BF16: k_render_batch<VDI_BF16><<<g, kBlock, 0, s>>>(jobs, njobs); break;
-        default: k_render_batch<VDI_F32><<<g, kBlock, 0, s>>>(jobs, njobs); break;
-        }
+    switch (fmt) {
+    case VDI_F16: return launch_batch_of<VDI_F16>(jobs, njobs, g, preview, wide, s);
+    case VDI_BF16: return launch_batch_of<VDI_BF16>(jobs, njobs, g, preview, wide, s);
+    default: return launch_batch_of<VDI_F32>(jobs, njobs, g, preview, wide, s);
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_batch_upsample(const UpsampleJob *jobs, int32_t njobs, uint32_t nblocks, hipStream_t s)

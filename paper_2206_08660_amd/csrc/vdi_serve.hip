@@ -191,6 +191,7 @@ void launch_batch(vdi_server_s *s, Lane &L)
     int nj = 0, nu = 0;
     int group_start[2][3], group_count[2][3];
     uint32_t group_blocks[2][3];
+    bool wide = false;
     for (int p = 0; p < 2; ++p)
         for (int f = 0; f < 3; ++f) {
             group_start[p][f] = nj;
@@ -201,6 +202,7 @@ void launch_batch(vdi_server_s *s, Lane &L)
                 t = align_up(t);
                 r.job.tile0 = (uint32_t)t;
                 t += r.job.ntiles;
+                wide = wide || !fits32(r.job.V.WO, r.job.V.HO, r.job.V.NS);
                 L.h_jobs[nj++] = r.job;
             }
             group_count[p][f] = nj - group_start[p][f];
@@ -222,7 +224,7 @@ void launch_batch(vdi_server_s *s, Lane &L)
         for (int f = 0; f < 3 && e == hipSuccess; ++f)
             if (group_count[p][f])
                 e = launch_batch_render(L.d_jobs + group_start[p][f], group_count[p][f], group_blocks[p][f], f, p == 1,
-                                        L.stream);
+                                        wide, L.stream);
     if (e == hipSuccess && nu) e = launch_batch_upsample(L.d_up, nu, (uint32_t)tu, L.stream);
     if (e == hipSuccess) e = hipEventRecord(L.done, L.stream);
     L.tickets = std::move(take);
@@ -709,6 +711,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         return set_error(VDI_ERR_ARG, "n must be in [1, %d] (got %d)", VDI_BATCH_MAX_FRAMES, n);
     if (!vdis || !cams || !widths || !heights || !D_I || !D_R || !outs) return set_error(VDI_ERR_ARG, "null array");
     std::vector<BatchItem> items((size_t)n);
+    bool wide = false;
     int device = -1;
     for (int i = 0; i < n; ++i) {
         int rc = check_render_args(vdis[i], &cams[i], widths[i], heights[i], D_I[i], D_R[i], outs[i]);
@@ -724,6 +727,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         rc = make_frame(S, cams[i], w, h, (double)widths[i] / (double)heights[i], it.job.F);
         if (rc) return set_error(rc, "frame %d: %s", i, vdi_last_error());
         it.job.V = S.dev;
+        wide = wide || !fits32(S.dev.WO, S.dev.HO, S.dev.NS);
         it.job.F.DR = D_R[i];
         it.job.F.ess = 1;
         it.job.F.search = VDI_SEARCH_WINDOW;
@@ -832,7 +836,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
     }
     for (const Launch &L : launches) {
         if (e != hipSuccess) break;
-        e = launch_batch_render(d_jobs + L.start, L.count, L.nblocks, L.fmt, L.preview, st);
+        e = launch_batch_render(d_jobs + L.start, L.count, L.nblocks, L.fmt, L.preview, wide, st);
     }
     for (const Launch &L : up_launches) {
         if (e != hipSuccess) break;

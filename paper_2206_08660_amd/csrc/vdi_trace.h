@@ -101,16 +101,26 @@ VDI_HD inline int xcd_tile(int bid, int tiles_x, int tiles_y, int band_rows = kB
 // ---------------------------------------------------------------------------
 // Colour planes
 // ---------------------------------------------------------------------------
+// Element i of a plane.  Idx = uint32_t: its byte offset fits 32 bits (fits32).
+template <typename T, typename Idx>
+VDI_HD inline const T *elem(const T *base, Idx i)
+{
+    if constexpr (sizeof(Idx) == 4)
+        return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
+    else
+        return base + i;
+}
+
 // Colour of slot idx.  FMT is the storage format, or kFmtRuntime to read it
 // from `fmt` (one code path for kernels that serve VDIs of any format).
 constexpr int kFmtRuntime = -1;
 
-template <int FMT>
-VDI_HD inline float4 load_rgba(const void *base, uint64_t idx, int fmt = FMT)
+template <int FMT, typename Idx>
+VDI_HD inline float4 load_rgba(const void *base, Idx idx, int fmt = FMT)
 {
     const int f = FMT >= 0 ? FMT : fmt;
-    if (FMT == VDI_F32 || (FMT < 0 && f == VDI_F32)) return VDI_LOAD(reinterpret_cast<const float4 *>(base) + idx, 3);
-    const uint2 u = VDI_LOAD(reinterpret_cast<const uint2 *>(base) + idx, 3);
+    if (FMT == VDI_F32 || (FMT < 0 && f == VDI_F32)) return VDI_LOAD(elem(static_cast<const float4 *>(base), idx), 3);
+    const uint2 u = VDI_LOAD(elem(static_cast<const uint2 *>(base), idx), 3);
     if (f == VDI_F16) {
         const __half2 rg = *reinterpret_cast<const __half2 *>(&u.x);
         const __half2 ba = *reinterpret_cast<const __half2 *>(&u.y);
@@ -129,11 +139,12 @@ struct Ray {
     double t0, t1;      // clipped parameter range (world distance from eye_N)
 };
 
-// Keep t with a + b t >= 0.
+// Keep t with a + b t >= 0.  A slope under 1e-300 is a zero: its crossing lies
+// beyond every ray, and its reciprocal beyond the double range.
 VDI_HD inline bool clip(double a, double b, double &lo, double &hi)
 {
-    if (b == 0.0) return a >= 0.0;
-    const double t = -a / b;
+    if (fabs(b) < 1e-300) return a >= 0.0;
+    const double t = -a * rcp64(b);
     if (b > 0.0)
         lo = fmax(lo, t);
     else
@@ -193,11 +204,20 @@ VDI_HD inline int cell_of(double ndc, int n, int dir)
     return min(max(i, 0), n - 1);
 }
 
-// cos of the angle between list (ix, iy)'s generating ray and V_O's axis.
-VDI_HD inline float list_cos(const DevVDI &V, int ix, int iy)
+// x / n for x = 1, 3, ..., 2 n - 1 and n <= 32768, correctly rounded, from
+// inv = 1 / n: 3 instructions for the 10 of a division (all such x and n
+// compared with the division).
+VDI_HD inline float div_odd(float x, float n, float inv)
 {
-    const float x = (-1.0f + (2.0f * ix + 1.0f) / V.WO) * V.tx_o;
-    const float y = (-1.0f + (2.0f * iy + 1.0f) / V.HO) * V.ty_o;
+    const float q = x * inv;
+    return fmaf(fmaf(-n, q, x), inv, q);
+}
+
+// cos of the angle between list (ix, iy)'s generating ray and V_O's axis.
+VDI_HD inline float list_cos(const DevVDI &V, const Frame &F, int ix, int iy)
+{
+    const float x = (-1.0f + div_odd(2.0f * ix + 1.0f, (float)V.WO, F.inv_wo)) * V.tx_o;
+    const float y = (-1.0f + div_odd(2.0f * iy + 1.0f, (float)V.HO, F.inv_ho)) * V.ty_o;
     return rsqrt32(1.0f + x * x + y * y);
 }
 
@@ -222,21 +242,20 @@ VDI_HD inline int slice_of(const float *gz, int gnz, double z, bool fwd)
 // Smallest j in [0, n) with b_j > z (n if none).  Back depths increase with j
 // because supersegments are sorted and disjoint.  Slot j of the list is
 // dep[base + j * stride].
-template <int SEARCH>
-VDI_HD inline int first_back_above(const float2 *__restrict__ dep, uint64_t stride, uint64_t base, int n,
-                                                double z, int p)
+template <int SEARCH, typename Idx>
+VDI_HD inline int first_back_above(const float2 *__restrict__ dep, Idx stride, Idx base, int n, double z, int p)
 {
     if constexpr (SEARCH == VDI_SEARCH_LINEAR) {
         int j = 0;
-        while (j < n && (double)VDI_LOAD(dep + ((uint64_t)j * stride + base), 2).y <= z) ++j;
+        while (j < n && (double)VDI_LOAD(elem(dep, (Idx)((Idx)j * stride + base)), 2).y <= z) ++j;
         return j;
     }
     int lo = 0, hi = n;
     if constexpr (SEARCH == VDI_SEARCH_SEEDED) {
         if (p >= 0 && p < n) {
             // Both candidate back depths are fetched before either is compared.
-            const float b1 = VDI_LOAD(dep + ((uint64_t)p * stride + base), 2).y;
-            const float b0 = p > 0 ? VDI_LOAD(dep + ((uint64_t)(p - 1) * stride + base), 2).y : -__builtin_huge_valf();
+            const float b1 = VDI_LOAD(elem(dep, (Idx)((Idx)p * stride + base)), 2).y;
+            const float b0 = p > 0 ? VDI_LOAD(elem(dep, (Idx)((Idx)(p - 1) * stride + base)), 2).y : -__builtin_huge_valf();
             if ((double)b0 > z)
                 hi = p - 1;  // the answer is at most p-1
             else if ((double)b1 > z)
@@ -247,7 +266,7 @@ VDI_HD inline int first_back_above(const float2 *__restrict__ dep, uint64_t stri
     }
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if ((double)VDI_LOAD(dep + ((uint64_t)mid * stride + base), 2).y > z)
+        if ((double)VDI_LOAD(elem(dep, (Idx)((Idx)mid * stride + base)), 2).y > z)
             hi = mid;
         else
             lo = mid + 1;
@@ -257,20 +276,19 @@ VDI_HD inline int first_back_above(const float2 *__restrict__ dep, uint64_t stri
 
 // Largest j in [0, n) with f_j < z (-1 if none): the first supersegment met by
 // a ray travelling towards smaller depth.
-template <int SEARCH>
-VDI_HD inline int last_front_below(const float2 *__restrict__ dep, uint64_t stride, uint64_t base, int n,
-                                                double z, int p)
+template <int SEARCH, typename Idx>
+VDI_HD inline int last_front_below(const float2 *__restrict__ dep, Idx stride, Idx base, int n, double z, int p)
 {
     if constexpr (SEARCH == VDI_SEARCH_LINEAR) {
         int j = n - 1;
-        while (j >= 0 && (double)VDI_LOAD(dep + ((uint64_t)j * stride + base), 2).x >= z) --j;
+        while (j >= 0 && (double)VDI_LOAD(elem(dep, (Idx)((Idx)j * stride + base)), 2).x >= z) --j;
         return j;
     }
     int lo = 0, hi = n;  // search the first j with f_j >= z
     if constexpr (SEARCH == VDI_SEARCH_SEEDED) {
         if (p >= 0 && p < n) {
-            const float f1 = VDI_LOAD(dep + ((uint64_t)p * stride + base), 2).x;
-            const float f2 = p + 1 < n ? VDI_LOAD(dep + ((uint64_t)(p + 1) * stride + base), 2).x : __builtin_huge_valf();
+            const float f1 = VDI_LOAD(elem(dep, (Idx)((Idx)p * stride + base)), 2).x;
+            const float f2 = p + 1 < n ? VDI_LOAD(elem(dep, (Idx)((Idx)(p + 1) * stride + base)), 2).x : __builtin_huge_valf();
             if ((double)f1 >= z)
                 hi = p;
             else if ((double)f2 >= z)
@@ -281,7 +299,7 @@ VDI_HD inline int last_front_below(const float2 *__restrict__ dep, uint64_t stri
     }
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if ((double)VDI_LOAD(dep + ((uint64_t)mid * stride + base), 2).x >= z)
+        if ((double)VDI_LOAD(elem(dep, (Idx)((Idx)mid * stride + base)), 2).x >= z)
             hi = mid;
         else
             lo = mid + 1;
@@ -311,16 +329,17 @@ constexpr int kWin = VDI_WIN;
 // and (double)x < z exactly when x < above(z), where below(z) is the largest
 // float <= z and above(z) the smallest float >= z.  The searches compare
 // float depths against these bounds, with the same outcome as comparing in
-// double precision.
+// double precision.  For z > 0, as depths along a ray are (it is clipped to
+// V_O's near plane): the neighbouring float is then one bit pattern away.
 VDI_HD inline float float_below(double z)
 {
     const float f = (float)z;
-    return (double)f > z ? nextafterf(f, -__builtin_huge_valf()) : f;
+    return __builtin_bit_cast(float, __builtin_bit_cast(int32_t, f) - ((double)f > z ? 1 : 0));
 }
 VDI_HD inline float float_above(double z)
 {
     const float f = (float)z;
-    return (double)f < z ? nextafterf(f, __builtin_huge_valf()) : f;
+    return __builtin_bit_cast(float, __builtin_bit_cast(int32_t, f) + ((double)f < z ? 1 : 0));
 }
 
 // A ray moving to larger depth usually finds its answer at or after the
@@ -369,14 +388,14 @@ VDI_HD inline int win_start_bwd(int p) { return p - kWin / 2; }
 #ifndef VDI_WIN2_SPREAD
 #define VDI_WIN2_SPREAD 2
 #endif
-template <bool SPREAD, int PICK = 0, typename Below>
-VDI_HD inline int window_search(const float2 *__restrict__ dep, uint64_t stride, uint64_t base, int n, int start,
+template <bool SPREAD, int PICK = 0, typename Idx, typename Below>
+VDI_HD inline int window_search(const float2 *__restrict__ dep, Idx stride, Idx base, int n, int start,
                                 Below below, float2 *pair = nullptr, bool *have = nullptr)
 {
     int lo = 0, hi = n;  // J in [lo, hi]
     if (n >= kWin) {
         const int w0 = max(0, min(start, n - kWin));
-        const float2 *w = dep + base + (uint64_t)w0 * stride;
+        const float2 *w = elem(dep, (Idx)(base + (Idx)w0 * stride));
         float2 b[kWin];
 #pragma unroll
         for (int k = 0; k < kWin; ++k) b[k] = VDI_LOAD(w + k * stride, 2);
@@ -404,7 +423,7 @@ VDI_HD inline int window_search(const float2 *__restrict__ dep, uint64_t stride,
                 if (lo >= hi) break;
                 // One more window next to the bracket, on the answer's side.
                 const int w1 = up ? min(lo, n - kWin) : max(0, hi - kWin);
-                const float2 *v = dep + base + (uint64_t)w1 * stride;
+                const float2 *v = elem(dep, (Idx)(base + (Idx)w1 * stride));
                 float2 c[kWin];
 #pragma unroll
                 for (int k = 0; k < kWin; ++k) c[k] = VDI_LOAD(v + k * stride, 2);
@@ -431,7 +450,7 @@ VDI_HD inline int window_search(const float2 *__restrict__ dep, uint64_t stride,
     if constexpr (!SPREAD) {
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (below(VDI_LOAD(dep + base + (uint64_t)mid * stride, 2)))
+            if (below(VDI_LOAD(elem(dep, (Idx)(base + (Idx)mid * stride)), 2)))
                 lo = mid + 1;
             else
                 hi = mid;
@@ -443,7 +462,7 @@ VDI_HD inline int window_search(const float2 *__restrict__ dep, uint64_t stride,
         const int span = hi - lo;
         float2 b[kWin];
 #pragma unroll
-        for (int k = 0; k < kWin; ++k) b[k] = VDI_LOAD(dep + base + (uint64_t)(lo + ((k + 1) * span) / (kWin + 1)) * stride, 2);
+        for (int k = 0; k < kWin; ++k) b[k] = VDI_LOAD(elem(dep, (Idx)(base + (Idx)(lo + ((k + 1) * span) / (kWin + 1)) * stride)), 2);
         int m = 0;
 #pragma unroll
         for (int k = 0; k < kWin; ++k) m += below(b[k]) ? 1 : 0;
@@ -455,7 +474,7 @@ VDI_HD inline int window_search(const float2 *__restrict__ dep, uint64_t stride,
     if (hi > lo) {
         // At most kWin candidate slots before hi: J is lo plus those below.
         const int len = hi - lo;
-        const float2 *w = dep + base + (uint64_t)lo * stride;
+        const float2 *w = elem(dep, (Idx)(base + (Idx)lo * stride));
         float2 b[kWin];
 #pragma unroll
         for (int k = 0; k < kWin; ++k) b[k] = VDI_LOAD(w + (uint64_t)min(k, len - 1) * stride, 2);
@@ -469,8 +488,8 @@ VDI_HD inline int window_search(const float2 *__restrict__ dep, uint64_t stride,
 
 // Smallest j in [0, n) with b_j > z (n if none); the window starts at slot
 // `start`.
-template <bool SPREAD = false>
-VDI_HD inline int first_back_above_win(const float2 *__restrict__ dep, uint64_t stride, uint64_t base, int n, double z,
+template <bool SPREAD = false, typename Idx>
+VDI_HD inline int first_back_above_win(const float2 *__restrict__ dep, Idx stride, Idx base, int n, double z,
                                        int start, float2 *pair = nullptr, bool *have = nullptr)
 {
     const float zb = float_below(z);  // b > z  <=>  b > zb
@@ -479,8 +498,8 @@ VDI_HD inline int first_back_above_win(const float2 *__restrict__ dep, uint64_t 
 
 // Largest j in [0, n) with f_j < z (-1 if none), window from `start`: one
 // less than the first j with f_j >= z, found as above.
-template <bool SPREAD = false>
-VDI_HD inline int last_front_below_win(const float2 *__restrict__ dep, uint64_t stride, uint64_t base, int n, double z,
+template <bool SPREAD = false, typename Idx>
+VDI_HD inline int last_front_below_win(const float2 *__restrict__ dep, Idx stride, Idx base, int n, double z,
                                        int start, float2 *pair = nullptr, bool *have = nullptr)
 {
     const float za = float_above(z);  // f < z  <=>  f < za
@@ -520,14 +539,19 @@ constexpr bool kWinColour = VDI_WIN_COLOUR != 0;
 
 // Element distance between slots j and j + 1 of a list: a compile-time
 // constant with bricks, so slot addresses need no multiply.
-VDI_HD inline uint64_t slot_stride(const DevVDI &V)
+template <typename Idx>
+VDI_HD inline Idx slot_stride(const DevVDI &V)
 {
-    if constexpr (kBrick != 0) return (uint64_t)kBrick;
-    return V.sstride;
+    if constexpr (kBrick != 0) return (Idx)kBrick;
+    return (Idx)V.sstride;
 }
 
 // Depth pair of slot j of the list whose storage starts at lb (list_base).
-VDI_HD inline float2 depth_at(const DevVDI &V, int j, uint64_t lb) { return VDI_LOAD(V.depth + (uint64_t)j * slot_stride(V) + lb, 2); }
+template <typename Idx>
+VDI_HD inline float2 depth_at(const DevVDI &V, int j, Idx lb)
+{
+    return VDI_LOAD(elem(V.depth, (Idx)((Idx)j * slot_stride<Idx>(V) + lb)), 2);
+}
 
 // Composite the part of list (ix, iy) that a ray with dz/dt = Zp crosses
 // between parameters ta and tb (Sections 4.2, Eq. 2).  n is the list's count
@@ -537,20 +561,20 @@ VDI_HD inline float2 depth_at(const DevVDI &V, int j, uint64_t lb) { return VDI_
 // compared, and the one that hits is reused); the next ones by adjacency,
 // each colour load overlapping the following depth load.  p is updated;
 // returns true once the ray has terminated.
-template <int FMT, int SEARCH, bool COUNT>
+template <int FMT, int SEARCH, bool COUNT, typename Idx>
 VDI_HDI bool do_list(const DevVDI &V, const Frame &F, int ix, int iy, int n, double ta, double tb, double Z0,
                     double Zp, double invZp, Accum &A, int &p, Counters &cnt)
 {
-    const uint64_t li = (uint64_t)iy * V.WO + ix;
+    [[maybe_unused]] const uint64_t li = (uint64_t)iy * V.WO + ix;
     if constexpr (COUNT) {
         F.touched_lists[li] = 1;
         ++cnt.lists;
     }
     if (n == 0) return false;
     const double za = Z0 + ta * Zp, zb = Z0 + tb * Zp;
-    const float cth = list_cos(V, ix, iy);
+    const float cth = list_cos(V, F, ix, iy);
     const float2 *__restrict__ dep = V.depth;
-    const uint64_t stride = slot_stride(V), lb = list_base_xy(ix, iy, V.NS, V.WO);
+    const Idx stride = slot_stride<Idx>(V), lb = list_base_xy<Idx>(ix, iy, V.NS, V.WO);
     auto piece = [&](int j, float2 d, float4 c, double zl, double zh, double inv) -> bool {
         composite(A, c, (float)((zh - zl) * inv) * cth * rcp32(d.y - d.x));
         if constexpr (COUNT) {
@@ -583,7 +607,7 @@ VDI_HDI bool do_list(const DevVDI &V, const Frame &F, int ix, int iy, int n, dou
                 d = dp;
                 have = true;
             } else {
-                j = p + 1 + first_back_above<VDI_SEARCH_BINARY>(dep, stride, lb + (uint64_t)(p + 1) * stride, n - p - 1,
+                j = p + 1 + first_back_above<VDI_SEARCH_BINARY>(dep, stride, (Idx)(lb + (Idx)(p + 1) * stride), n - p - 1,
                                                                  za, -1);
             }
         } else {
@@ -595,13 +619,13 @@ VDI_HDI bool do_list(const DevVDI &V, const Frame &F, int ix, int iy, int n, dou
         if (j < n && !have) {
             d = depth_at(V, j, lb);
             if constexpr (kWinColour && SEARCH == VDI_SEARCH_WINDOW) {
-                c0 = load_rgba<FMT>(V.rgba, (uint64_t)j * stride + lb, V.fmt);
+                c0 = load_rgba<FMT>(V.rgba, (Idx)((Idx)j * stride + lb), V.fmt);
                 have_c = true;
             }
         }
         while (j < n) {
             if ((double)d.x >= zb) break;
-            const float4 c = have_c ? c0 : load_rgba<FMT>(V.rgba, (uint64_t)j * stride + lb, V.fmt);
+            const float4 c = have_c ? c0 : load_rgba<FMT>(V.rgba, (Idx)((Idx)j * stride + lb), V.fmt);
             have_c = false;
             const bool more = (double)d.y < zb && j + 1 < n;
             const float2 dn = more ? depth_at(V, j + 1, lb) : d;
@@ -639,7 +663,7 @@ VDI_HDI bool do_list(const DevVDI &V, const Frame &F, int ix, int iy, int n, dou
                 d = dp;
                 have = true;
             } else {
-                j = p + 2 + last_front_below<VDI_SEARCH_BINARY>(dep, stride, lb + (uint64_t)(p + 2) * stride, n - p - 2,
+                j = p + 2 + last_front_below<VDI_SEARCH_BINARY>(dep, stride, (Idx)(lb + (Idx)(p + 2) * stride), n - p - 2,
                                                                  za, -1);
             }
         } else {
@@ -651,13 +675,13 @@ VDI_HDI bool do_list(const DevVDI &V, const Frame &F, int ix, int iy, int n, dou
         if (j >= 0 && !have) {
             d = depth_at(V, j, lb);
             if constexpr (kWinColour && SEARCH == VDI_SEARCH_WINDOW) {
-                c0 = load_rgba<FMT>(V.rgba, (uint64_t)j * stride + lb, V.fmt);
+                c0 = load_rgba<FMT>(V.rgba, (Idx)((Idx)j * stride + lb), V.fmt);
                 have_c = true;
             }
         }
         while (j >= 0) {
             if ((double)d.y <= zb) break;
-            const float4 c = have_c ? c0 : load_rgba<FMT>(V.rgba, (uint64_t)j * stride + lb, V.fmt);
+            const float4 c = have_c ? c0 : load_rgba<FMT>(V.rgba, (Idx)((Idx)j * stride + lb), V.fmt);
             have_c = false;
             const bool more = (double)d.x > zb && j > 0;
             const float2 dn = more ? depth_at(V, j - 1, lb) : d;
@@ -679,7 +703,7 @@ VDI_HDI bool do_list(const DevVDI &V, const Frame &F, int ix, int iy, int n, dou
         for (int j = 0; j < n; ++j) {
             const float2 d = depth_at(V, j, lb);
             if ((double)d.x <= za && za < (double)d.y) {
-                const float4 c = load_rgba<FMT>(V.rgba, (uint64_t)j * stride + lb, V.fmt);
+                const float4 c = load_rgba<FMT>(V.rgba, (Idx)((Idx)j * stride + lb), V.fmt);
                 p = j;
                 composite(A, c, (float)(tb - ta) * cth * rcp32(d.y - d.x));
                 if constexpr (COUNT) {
@@ -708,12 +732,12 @@ VDI_HD inline bool cell_occupied(const DevVDI &V, int cell)
 // 4.1), fetching the count of the list it enters next while it composites the
 // current one; with ESS on it crosses grid cells of count 0 in one step
 // (Section 4.3), keeping the current cell and depth slice from step to step.
-template <int FMT, int SEARCH, bool ESS, bool COUNT>
+template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx = uint64_t>
 VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, int px, int py, Counters &cnt)
 {
     Accum A = {0.0f, 0.0f, 0.0f, 1.0f};
     Ray r;
-    const double xc = -1.0 + (2.0 * px + 1.0) / F.W, yc = -1.0 + (2.0 * py + 1.0) / F.H;
+    const double xc = -1.0 + (2.0 * px + 1.0) * F.inv_w, yc = -1.0 + (2.0 * py + 1.0) * F.inv_h;
     if (!ray_setup(F, xc, yc, r)) return make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const int WO = V.WO, HO = V.HO, gk = V.gk;
     // Direction of travel across the list grid: d/dt (X/Z) has the sign of Kx.
@@ -748,7 +772,7 @@ VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, i
     };
     locate(t);
     int p = -1;
-    int n = VDI_LOAD(V.count + (uint64_t)iy * WO + ix, 0);
+    int n = VDI_LOAD(elem(V.count, (Idx)((Idx)iy * (Idx)WO + (Idx)ix)), 0);
     // Every iteration moves one list or jumps a grid cell; the cap only
     // guards against a loop that does not advance.
     const int max_iter = 4 * (WO + HO) + 4 * V.gnz + 64;
@@ -795,7 +819,7 @@ VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, i
                 if (cell_occupied(V, cell)) {
                     cellmode = false;
                     locate(t);
-                    n = VDI_LOAD(V.count + (uint64_t)iy * WO + ix, 0);
+                    n = VDI_LOAD(elem(V.count, (Idx)((Idx)iy * (Idx)WO + (Idx)ix)), 0);
                     ccell = -1;
                 }
                 continue;
@@ -838,8 +862,8 @@ VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, i
         const bool stepx = tx <= ty;
         const int nx = stepx ? ix + sx : ix, ny = stepx ? iy : iy + sy;
         const bool more = tn < r.t1 && (unsigned)nx < (unsigned)WO && (unsigned)ny < (unsigned)HO;
-        const int n_next = more ? VDI_LOAD(V.count + (uint64_t)ny * WO + nx, 0) : 0;
-        if (tn > t && do_list<FMT, SEARCH, COUNT>(V, F, ix, iy, n, t, tn, F.Z0, r.Zp, invZp, A, p, cnt)) break;
+        const int n_next = more ? VDI_LOAD(elem(V.count, (Idx)((Idx)ny * (Idx)WO + (Idx)nx)), 0) : 0;
+        if (tn > t && do_list<FMT, SEARCH, COUNT, Idx>(V, F, ix, iy, n, t, tn, F.Z0, r.Zp, invZp, A, p, cnt)) break;
         if (!more) break;
         {
             // One crossing solve per step, for the axis the ray stepped in.
@@ -877,13 +901,13 @@ constexpr double kTieShift = 1e-9;
 // it read (touched_cells), the list of every sample (touched_lists) and every
 // supersegment it composited (touched_slots), counted in cnt as samples
 // (lists) and pieces.
-template <int FMT, bool COUNT = false>
+template <int FMT, bool COUNT = false, typename Idx = uint64_t>
 VDI_HDI Accum trace_preview(const DevVDI &V, const Frame &F, const float *s_gz, int px, int py, int part = 0,
                            int parts = 1, Counters *cnt = nullptr)
 {
     Accum A = {0.0f, 0.0f, 0.0f, 1.0f};
     Ray r;
-    const double xc = -1.0 + (2.0 * px + 1.0) / F.W, yc = -1.0 + (2.0 * py + 1.0) / F.H;
+    const double xc = -1.0 + (2.0 * px + 1.0) * F.inv_w, yc = -1.0 + (2.0 * py + 1.0) * F.inv_h;
     if (ray_setup(F, xc, yc, r)) {
         const int WO = V.WO, HO = V.HO, k = V.gk;
         const double Kx = r.Xp * F.Z0 - F.X0 * r.Zp, Ky = r.Yp * F.Z0 - F.Y0 * r.Zp;
@@ -894,7 +918,7 @@ VDI_HDI Accum trace_preview(const DevVDI &V, const Frame &F, const float *s_gz, 
         const double invZp = flat ? 0.0 : rcp64(r.Zp);
         const double inv_k2 = 1.0 / (double)(k * k);
         const float2 *__restrict__ dep = V.depth;
-        const uint64_t stride = slot_stride(V);
+        const Idx stride = slot_stride<Idx>(V);
         double t = r.t0;
         int cx, cy, cz, mx, my;
         double tx, ty, tz;
@@ -1082,7 +1106,7 @@ VDI_HDI Accum trace_preview(const DevVDI &V, const Frame &F, const float *s_gz, 
                         h = (tn - t) / n;
                         q = 0;
                         sample_list(0, u, z, lx, ly);
-                        nl = VDI_LOAD(V.count + ((uint64_t)ly * WO + lx), 0);
+                        nl = VDI_LOAD(elem(V.count, (Idx)((Idx)ly * (Idx)WO + (Idx)lx)), 0);
                         advance = false;
                     }
                 }
@@ -1090,21 +1114,21 @@ VDI_HDI Accum trace_preview(const DevVDI &V, const Frame &F, const float *s_gz, 
                 double un = 0.0, zn = 0.0;
                 int lxn = lx, lyn = ly;
                 if (q + 1 < n) sample_list(q + 1, un, zn, lxn, lyn);
-                const int nln = q + 1 < n ? (int)VDI_LOAD(V.count + ((uint64_t)lyn * WO + lxn), 0) : 0;
+                const int nln = q + 1 < n ? (int)VDI_LOAD(elem(V.count, (Idx)((Idx)lyn * (Idx)WO + (Idx)lxn)), 0) : 0;
                 if constexpr (COUNT) {
                     F.touched_lists[(uint64_t)ly * WO + lx] = 1;
                     ++cnt->lists;
                 }
                 if (nl > 0) {
                     // Point location: the supersegment with f <= z < b.
-                    const uint64_t lb = list_base_xy(lx, ly, V.NS, WO);
+                    const Idx lb = list_base_xy<Idx>(lx, ly, V.NS, WO);
                     const int j = first_back_above_win<true>(dep, stride, lb, nl, z, fwd ? win_start_fwd(p) : win_start_bwd(p));
                     if (j < nl) {
-                        const float2 fb = VDI_LOAD(dep + ((uint64_t)j * stride + lb), 2);
+                        const float2 fb = VDI_LOAD(elem(dep, (Idx)((Idx)j * stride + lb)), 2);
                         p = j;
                         if ((double)fb.x <= z) {
-                            const float4 c = load_rgba<FMT>(V.rgba, (uint64_t)j * stride + lb, V.fmt);
-                            composite(A, c, (float)h * list_cos(V, lx, ly) * rcp32(fb.y - fb.x));
+                            const float4 c = load_rgba<FMT>(V.rgba, (Idx)((Idx)j * stride + lb), V.fmt);
+                            composite(A, c, (float)h * list_cos(V, F, lx, ly) * rcp32(fb.y - fb.x));
                             if constexpr (COUNT) {
                                 F.touched_slots[(uint64_t)j * V.plane + (uint64_t)ly * WO + lx] = 1;
                                 ++cnt->pieces;
