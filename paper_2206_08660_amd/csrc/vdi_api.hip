@@ -127,6 +127,31 @@ int build_frame(const vdi::VdiSet &S, const vdi_camera &cam, int w, int h, doubl
     f.inv_h = 1.0 / h;
     f.W = w;
     f.H = h;
+    // Where the AABB lies on the image: the bounds of its projected corners, one
+    // pixel wider, or everything if a corner is not well in front of the eye.
+    f.rx1 = w;
+    f.ry1 = h;
+    double x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+    bool front = true;
+    for (int m = 0; m < 8; ++m) {
+        double q[3];
+        for (int a = 0; a < 3; ++a) q[a] = (m >> a & 1 ? f.bmax[a] : f.bmin[a]) - f.eyeN[a];
+        const double z = dot(f.FN, q);
+        front = front && z > 1e-6 * norm(q);
+        const double x = (dot(f.RN, q) / (z * f.tx_n) + 1.0) * w / 2.0, y = (dot(f.UN, q) / (z * f.ty_n) + 1.0) * h / 2.0;
+        x0 = std::min(x0, x);
+        x1 = std::max(x1, x);
+        y0 = std::min(y0, y);
+        y1 = std::max(y1, y);
+    }
+    if (front && isfinite(x0) && isfinite(x1) && isfinite(y0) && isfinite(y1)) {
+        // Pixel p has its centre at p + 0.5.
+        auto pixel = [](double v, int n) { return (int32_t)std::min(std::max(v, 0.0), (double)n); };
+        f.rx0 = pixel(floor(x0) - 1.0, w);
+        f.rx1 = pixel(ceil(x1) + 1.0, w);
+        f.ry0 = pixel(floor(y0) - 1.0, h);
+        f.ry1 = pixel(ceil(y1) + 1.0, h);
+    }
     f.ess = 1;
     f.search = VDI_SEARCH_WINDOW;
     f.parts = vdi::preview_parts(w, h);

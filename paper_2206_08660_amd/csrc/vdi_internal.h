@@ -153,6 +153,7 @@ struct Frame {
     float inv_wo, inv_ho;      // 1 / WO, 1 / HO (list_cos)
     double inv_w, inv_h;       // 1 / W, 1 / H
     int32_t W, H;              // rays cast
+    int32_t rx0, ry0, rx1, ry1;  // pixels [rx0, rx1) x [ry0, ry1) hold every ray that can meet the AABB
     int32_t ess, search;
     double DR;                 // > 0: along-ray subsampling
     int32_t parts;             // preview: lanes per ray (preview_parts)

@@ -40,29 +40,6 @@ namespace {
 #endif
 #define VDI_EXACT_OCC __attribute__((amdgpu_waves_per_eu(VDI_EXACT_WAVES)))
 
-template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx>
-__global__ __launch_bounds__(kBlock) VDI_EXACT_OCC void k_render_exact(DevVDI V, Frame F)
-{
-    __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
-    if constexpr (ESS) {
-        for (int i = threadIdx.x; i <= V.gnz; i += kBlock) s_gz[i] = V.gz[i];
-        __syncthreads();
-    }
-    const int tiles_x = (F.W + kXTileW - 1) / kXTileW, tiles_y = (F.H + kXTileH - 1) / kXTileH;
-    const int tile = xcd_tile(blockIdx.x, tiles_x, tiles_y, kXBandRows);
-    const int px = (tile % tiles_x) * kXTileW + (threadIdx.x % kXTileW);
-    const int py = (tile / tiles_x) * kXTileH + (threadIdx.x / kXTileW);
-    if (px >= F.W || py >= F.H) return;
-    Counters cnt = {0, 0};
-    F.out[(uint64_t)py * F.W + px] = trace_exact<FMT, SEARCH, ESS, COUNT, Idx>(V, F, s_gz, px, py, cnt);
-    if constexpr (COUNT) {
-        if (F.ray_stats) {
-            F.ray_stats[2 * ((uint64_t)py * F.W + px)] = cnt.lists;
-            F.ray_stats[2 * ((uint64_t)py * F.W + px) + 1] = cnt.pieces;
-        }
-    }
-}
-
 // Store of an output pixel: plain, or (WT) written through to device memory
 // as two relaxed system-scope atomic stores of 8 bytes, for the persistent
 // kernel, whose results are read by other workgroups and by the host with no
@@ -81,6 +58,104 @@ __device__ __forceinline__ void store_px(float4 *p, float4 v)
     }
 }
 
+// First pixel of tile `bid` of a frame in tiles of tw x th rays; false if no ray
+// of the tile can meet the AABB (Frame::rx0 ...).  Such tiles are transparent
+// and leave without setting up their rays, which takes about as long as 20
+// list steps (1080p workload: two tiles in three; 32,000 of them take 40 us).
+// They come last.  The tiles that meet the AABB are dealt to the XCDs in bands
+// of `band` tile rows (xcd_tile).
+__device__ __forceinline__ bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &x0, int &y0)
+{
+    const int tiles_x = (F.W + tw - 1) / tw, tiles_y = (F.H + th - 1) / th;
+    const int cx0 = F.rx0 / tw, cx1 = (F.rx1 + tw - 1) / tw, cy0 = F.ry0 / th, cy1 = (F.ry1 + th - 1) / th;
+    const int nx = max(cx1 - cx0, 0), ny = nx > 0 ? max(cy1 - cy0, 0) : 0, inside = nx * ny;
+    if (bid < inside) {
+        const int t = xcd_tile(bid, nx, ny, band);
+        x0 = (cx0 + t % nx) * tw;
+        y0 = (cy0 + t / nx) * th;
+        return true;
+    }
+    // The others: whole rows below and above the AABB's, then the ends of its rows.
+    int k = bid - inside;
+    const int rows = tiles_y - ny, ends = tiles_x - nx;
+    if (ny == 0 || k < rows * tiles_x) {
+        const int r = k / tiles_x;
+        x0 = (k % tiles_x) * tw;
+        y0 = (ny == 0 || r < cy0 ? r : r + ny) * th;
+    } else {
+        k -= rows * tiles_x;
+        const int c = k % ends;
+        x0 = (c < cx0 ? c : c + nx) * tw;
+        y0 = (cy0 + k / ends) * th;
+    }
+    return false;
+}
+
+// One exact tile of kXTileW x kXTileH rays.
+template <int FMT, int SEARCH, bool ESS, typename Idx, bool WT = false>
+__device__ __forceinline__ void exact_tile(const DevVDI &V, const Frame &F, const float *s_gz, int tile_index)
+{
+    int x0, y0;
+    const bool meets = place_tile(F, kXTileW, kXTileH, kXBandRows, tile_index, x0, y0);
+    const int px = x0 + (int)threadIdx.x % kXTileW, py = y0 + (int)threadIdx.x / kXTileW;
+    if (px >= F.W || py >= F.H) return;
+    float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (meets) {
+        Counters cnt = {0, 0};
+        o = trace_exact<FMT, SEARCH, ESS, false, Idx>(V, F, s_gz, px, py, cnt);
+    }
+    store_px<WT>(&F.out[(uint64_t)py * F.W + px], o);
+}
+
+// Arguments of a single render's kernel, read where they are used.  Read
+// through the kernel's parameter they are all loaded at its start, over a
+// hundred scalar registers' worth, and spilled: 567 of the exact kernel's
+// instructions then moved them back, lane by lane (1080p f16 20 deg: 750 us
+// against 635 with the same tile order).
+struct RenderArgs {
+    DevVDI V;
+    Frame F;
+};
+__device__ __forceinline__ const RenderArgs &render_args(const RenderArgs &param)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    using Args = const __attribute__((address_space(4))) RenderArgs;
+    auto *p = (Args *)__builtin_amdgcn_kernarg_segment_ptr();  // the only parameter
+    asm volatile("" : "+s"(p));
+    return *(const RenderArgs *)p;
+#else
+    return param;
+#endif
+}
+
+template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx>
+__global__ __launch_bounds__(kBlock) VDI_EXACT_OCC void k_render_exact(RenderArgs args)
+{
+    const RenderArgs &A = render_args(args);
+    const DevVDI &V = A.V;
+    const Frame &F = A.F;
+    __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
+    if constexpr (ESS) {
+        for (int i = threadIdx.x; i <= V.gnz; i += kBlock) s_gz[i] = V.gz[i];
+        __syncthreads();
+    }
+    if constexpr (!COUNT) {
+        exact_tile<FMT, SEARCH, ESS, Idx>(V, F, s_gz, (int)blockIdx.x);
+    } else {
+        const int tiles_x = (F.W + kXTileW - 1) / kXTileW, tiles_y = (F.H + kXTileH - 1) / kXTileH;
+        const int tile = xcd_tile(blockIdx.x, tiles_x, tiles_y, kXBandRows);
+        const int px = (tile % tiles_x) * kXTileW + (threadIdx.x % kXTileW);
+        const int py = (tile / tiles_x) * kXTileH + (threadIdx.x / kXTileW);
+        if (px >= F.W || py >= F.H) return;
+        Counters cnt = {0, 0};
+        F.out[(uint64_t)py * F.W + px] = trace_exact<FMT, SEARCH, ESS, COUNT, Idx>(V, F, s_gz, px, py, cnt);
+        if (F.ray_stats) {
+            F.ray_stats[2 * ((uint64_t)py * F.W + px)] = cnt.lists;
+            F.ray_stats[2 * ((uint64_t)py * F.W + px) + 1] = cnt.pieces;
+        }
+    }
+}
+
 // One preview tile (preview_tile_dims): tw x th rays, F.parts adjacent lanes
 // per ray.  Lanes outside the image take part in the combination with an
 // empty result.
@@ -90,16 +165,17 @@ __device__ __forceinline__ void preview_tile(const DevVDI &V, const Frame &F, co
     const int parts = F.parts;
     int tw, th;
     preview_tile_dims(parts, tw, th);
-    const int tiles_x = (F.W + tw - 1) / tw, tiles_y = (F.H + th - 1) / th;
-    const int tile = xcd_tile(tile_index, tiles_x, tiles_y, VDI_BAND_ROWS / th > 0 ? VDI_BAND_ROWS / th : 1);
+    int x0, y0;
+    const bool meets = place_tile(F, tw, th, VDI_BAND_ROWS / th > 0 ? VDI_BAND_ROWS / th : 1, tile_index, x0, y0);
     const int lane = threadIdx.x, ray = lane / parts;
-    const int px = (tile % tiles_x) * tw + ray % tw;
-    const int py = (tile / tiles_x) * th + ray / tw;
+    const int px = x0 + ray % tw, py = y0 + ray / tw;
     const bool in = px < F.W && py < F.H;
     Accum a = {0.0f, 0.0f, 0.0f, 1.0f};
     Counters cnt = {0, 0};
-    if (in) a = trace_preview<FMT, COUNT, Idx>(V, F, s_gz, px, py, lane % parts, parts, &cnt);
-    a = combine_parts(a, parts, lane);
+    if (meets) {
+        if (in) a = trace_preview<FMT, COUNT, Idx>(V, F, s_gz, px, py, lane % parts, parts, &cnt);
+        a = combine_parts(a, parts, lane);
+    }
     if (in && lane % parts == 0) store_px<WT>(&F.out[(uint64_t)py * F.W + px], to_rgba(a));
     if constexpr (COUNT) {
         if (in && F.ray_stats) {
@@ -110,8 +186,11 @@ __device__ __forceinline__ void preview_tile(const DevVDI &V, const Frame &F, co
 }
 
 template <int FMT, bool COUNT, typename Idx>
-__global__ __launch_bounds__(kBlock) void k_render_preview(DevVDI V, Frame F)
+__global__ __launch_bounds__(kBlock) void k_render_preview(RenderArgs args)
 {
+    const RenderArgs &A = render_args(args);
+    const DevVDI &V = A.V;
+    const Frame &F = A.F;
     __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
     for (int i = threadIdx.x; i <= V.gnz; i += kBlock) s_gz[i] = V.gz[i];
     __syncthreads();
@@ -148,13 +227,7 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
     if constexpr (PREVIEW) {
         preview_tile<FMT, Idx>(J.V, J.F, s_gz, (int)local);
     } else {
-        const int tiles_x = (J.F.W + kXTileW - 1) / kXTileW, tiles_y = (J.F.H + kXTileH - 1) / kXTileH;
-        const int tile = xcd_tile((int)local, tiles_x, tiles_y, kXBandRows);
-        const int px = (tile % tiles_x) * kXTileW + (threadIdx.x % kXTileW);
-        const int py = (tile / tiles_x) * kXTileH + (threadIdx.x / kXTileW);
-        if (px >= J.F.W || py >= J.F.H) return;
-        Counters cnt = {0, 0};
-        J.F.out[(uint64_t)py * J.F.W + px] = trace_exact<FMT, VDI_SEARCH_WINDOW, true, false, Idx>(J.V, J.F, s_gz, px, py, cnt);
+        exact_tile<FMT, VDI_SEARCH_WINDOW, true, Idx>(J.V, J.F, s_gz, (int)local);
     }
 }
 
@@ -344,15 +417,7 @@ __global__ __launch_bounds__(kBlock) VDI_PERSIST_OCC void k_persist(const PHost 
             if (J.preview) {
                 preview_tile<FMT, uint64_t, false, true>(J.R.V, J.R.F, s_gz, (int)local);
             } else {
-                const int tiles_x = (J.R.F.W + kXTileW - 1) / kXTileW, tiles_y = (J.R.F.H + kXTileH - 1) / kXTileH;
-                const int tile = xcd_tile((int)local, tiles_x, tiles_y, kXBandRows);
-                const int px = (tile % tiles_x) * kXTileW + (lane % kXTileW);
-                const int py = (tile / tiles_x) * kXTileH + (lane / kXTileW);
-                if (px < J.R.F.W && py < J.R.F.H) {
-                    Counters cnt = {0, 0};
-                    store_px<true>(&J.R.F.out[(uint64_t)py * J.R.F.W + px],
-                                   trace_exact<FMT, VDI_SEARCH_WINDOW, true, false>(J.R.V, J.R.F, s_gz, px, py, cnt));
-                }
+                exact_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
             }
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores have completed
             __syncthreads();                // and s_gz is free for the next tile
@@ -592,7 +657,7 @@ hipError_t launch_exact_fmt(const DevVDI &v, const Frame &f, dim3 grid, hipStrea
     default:
         if (!ess) k = k_render_exact<FMT, VDI_SEARCH_SEEDED, false, COUNT, Idx>;
     }
-    k<<<grid, kBlock, 0, s>>>(v, f);
+    k<<<grid, kBlock, 0, s>>>(RenderArgs{v, f});
     return hipGetLastError();
 }
 
@@ -605,7 +670,7 @@ hipError_t launch_exact_of(const DevVDI &v, const Frame &f, bool counters, dim3 
     if (f.search != VDI_SEARCH_WINDOW || !fits32(v.WO, v.HO, v.NS)) return launch_exact_fmt<FMT, false, uint64_t>(v, f, grid, s);
     auto k = f.ess ? k_render_exact<FMT, VDI_SEARCH_WINDOW, true, false, uint32_t>
                    : k_render_exact<FMT, VDI_SEARCH_WINDOW, false, false, uint32_t>;
-    k<<<grid, kBlock, 0, s>>>(v, f);
+    k<<<grid, kBlock, 0, s>>>(RenderArgs{v, f});
     return hipGetLastError();
 }
 
@@ -631,7 +696,7 @@ hipError_t launch_preview_of(const DevVDI &v, const Frame &f, bool counters, dim
 {
     auto k = counters ? k_render_preview<FMT, true, uint64_t>
                       : (fits32(v.WO, v.HO, v.NS) ? k_render_preview<FMT, false, uint32_t> : k_render_preview<FMT, false, uint64_t>);
-    k<<<grid, kBlock, 0, s>>>(v, f);
+    k<<<grid, kBlock, 0, s>>>(RenderArgs{v, f});
     return hipGetLastError();
 }
 
