@@ -15,7 +15,7 @@
 #include <thread>
 #include <vector>
 
-#include "vdi_internal.h"
+#include "vdi_trace.h"
 
 namespace vdi {
 std::atomic<uint64_t> g_mem_epoch{0};
@@ -89,6 +89,23 @@ int make_basis(const vdi_camera &c, Basis &b)
 
 double dot(const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
 
+// The most lists that 3 x 3 rays over the AABB's part of the image cross (where
+// exact_parts asks).
+double lists_crossed(const vdi::DevVDI &V, const vdi::Frame &f)
+{
+    double most = 0.0;
+    if ((double)f.W * f.H > VDI_EXACT_LANES) return most;
+    for (int i = 0; i < 9; ++i) {
+        const double px = f.rx0 + (f.rx1 - f.rx0) * (0.1 + 0.4 * (i % 3)), py = f.ry0 + (f.ry1 - f.ry0) * (0.1 + 0.4 * (i / 3));
+        vdi::Ray r;
+        if (!vdi::ray_setup(f, -1.0 + 2.0 * px / f.W, -1.0 + 2.0 * py / f.H, r)) continue;
+        const double z0 = f.Z0 + r.t0 * r.Zp, z1 = f.Z0 + r.t1 * r.Zp;
+        most = std::max(most, fabs((f.X0 + r.t1 * r.Xp) / z1 - (f.X0 + r.t0 * r.Xp) / z0) * V.WO / 2 +
+                                  fabs((f.Y0 + r.t1 * r.Yp) / z1 - (f.Y0 + r.t0 * r.Yp) / z0) * V.HO / 2);
+    }
+    return most;
+}
+
 // Frame constants for rays on a w x h grid with aspect `aspect`, for the VDI set S.
 int build_frame(const vdi::VdiSet &S, const vdi_camera &cam, int w, int h, double aspect, vdi::Frame &f)
 {
@@ -155,6 +172,7 @@ int build_frame(const vdi::VdiSet &S, const vdi_camera &cam, int w, int h, doubl
     f.ess = 1;
     f.search = VDI_SEARCH_WINDOW;
     f.parts = vdi::preview_parts(w, h);
+    f.xparts = vdi::exact_parts(w, h, lists_crossed(S.dev, f));
     return VDI_OK;
 }
 
@@ -877,7 +895,11 @@ int vdi_render_counters(vdi_t v, const vdi_camera *cam, int32_t W, int32_t H, co
     f.touched_lists = touched_lists;
     f.touched_slots = touched_slots;
     f.ray_stats = ray_stats;
+    // The counters' walk takes every ray whole; the image is then vdi_render's,
+    // whose rays may be split.
     HIP_OR_FAIL(vdi::launch_render_exact(S.dev, f, true, static_cast<hipStream_t>(stream)), "counter render launch");
+    if (f.xparts > 1)
+        HIP_OR_FAIL(vdi::launch_render_exact(S.dev, f, false, static_cast<hipStream_t>(stream)), "counter render launch");
     HIP_OR_FAIL(vdi::note_use(v, static_cast<hipStream_t>(stream)), "render bookkeeping");
     return VDI_OK;
 }

@@ -36,6 +36,42 @@ constexpr int kXTileW = VDI_EXACT_TW;
 constexpr int kXTileH = 64 / VDI_EXACT_TW;
 constexpr int kXcds = 8;
 
+// Exact rays of small frames are split over `parts` adjacent lanes, by cutting
+// their parameter range: such a frame lasts as long as its longest ray, whose
+// lists follow one another.  A power of two up to 16 that keeps the launch
+// within 2^18 lanes (2^19 where rays cross 128 lists or more), and a part at
+// one list or more: `lists` is the most that the frame's rays cross, as its
+// set-up estimates.  Where the line lies (us, whole rays -> split; 1280 x 720 /
+// N_S 20 VDI at 30 deg, 128 x 128 / N_S 16 VDI at 5 deg): 128 x 128 frame 941
+// -> 114, 50 -> 26; 256 x 256 941 -> 260, 50 -> 36; 512 x 512 965 -> 703; but
+// 1280 x 720 1053 -> 1017 alone and 6560 -> 7560 in a server's mix, since
+// split rays cost set-up and shared lines that a full device pays for.
+#ifndef VDI_EXACT_LANES
+#define VDI_EXACT_LANES 262144
+#endif
+inline int exact_parts(int w, int h, double lists)
+{
+    const double lanes = lists >= 128.0 ? 2.0 * VDI_EXACT_LANES : VDI_EXACT_LANES;
+    int p = 1;
+    while (p < 16 && (double)w * h * p * 2 <= lanes && lists >= p * 2.0) p <<= 1;
+    return p;
+}
+// An exact wavefront renders 64 / parts rays, at most kXTileH rows tall; the
+// `parts` lanes of a ray are adjacent.
+__host__ __device__ inline void exact_tile_dims(int parts, int &tw, int &th)
+{
+    const int rays = 64 / parts;
+    th = rays < kXTileH ? rays : kXTileH;
+    tw = rays / th;
+}
+// Workgroups (one wavefront each) of an exact launch over w x h rays.
+__host__ __device__ inline uint32_t exact_tiles(int w, int h, int parts)
+{
+    int tw, th;
+    exact_tile_dims(parts, tw, th);
+    return (uint32_t)(((w + tw - 1) / tw) * ((h + th - 1) / th));
+}
+
 // Preview rays are split over `parts` adjacent lanes when there are few of
 // them: a preview frame lasts about as long as its longest ray's chain of
 // dependent loads, and with fewer rays than about two wavefronts per SIMD
@@ -157,6 +193,7 @@ struct Frame {
     int32_t ess, search;
     double DR;                 // > 0: along-ray subsampling
     int32_t parts;             // preview: lanes per ray (preview_parts)
+    int32_t xparts;            // exact: lanes per ray (exact_parts)
     float4 *out;               // [H][W]
     // counters (instrumented kernels only)
     uint8_t *touched_lists, *touched_slots, *touched_cells;
@@ -332,7 +369,10 @@ hipError_t launch_set_gz(const float *z, int32_t n, float *gz, hipStream_t strea
 // tile0, all of colour format fmt; nblocks covers the last job's tiles.
 // Exact jobs use the window search with empty-space skipping.  wide: some
 // job's VDI does not fit 32-bit offsets (fits32).
-hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, bool preview,
+// Kinds of jobs, each with a kernel of its own.
+enum JobKind { kExactJob, kSplitJob, kPreviewJob, kJobKinds };
+inline JobKind job_kind(bool preview, const Frame &f) { return preview ? kPreviewJob : (f.xparts > 1 ? kSplitJob : kExactJob); }
+hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, JobKind kind,
                                bool wide, hipStream_t stream);
 hipError_t launch_batch_upsample(const UpsampleJob *jobs, int32_t njobs, uint32_t nblocks, hipStream_t stream);
 // Persistent served launch of `blocks` workgroups (see PHost, PQueue; jobs

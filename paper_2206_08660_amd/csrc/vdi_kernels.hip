@@ -39,6 +39,13 @@ namespace {
 #define VDI_EXACT_WAVES 6
 #endif
 #define VDI_EXACT_OCC __attribute__((amdgpu_waves_per_eu(VDI_EXACT_WAVES)))
+// Batched exact tiles keep the device full for several frames on end: 7
+// wavefronts per SIMD (72 VGPRs) there, which a single frame loses 1-2% by.
+// Twelve 1080p frames 3142 -> 3111 us, served mix 6768 -> 6530 us.
+#ifndef VDI_BATCH_WAVES
+#define VDI_BATCH_WAVES 7
+#endif
+#define VDI_BATCH_OCC __attribute__((amdgpu_waves_per_eu(VDI_BATCH_WAVES)))
 
 // Store of an output pixel: plain, or (WT) written through to device memory
 // as two relaxed system-scope atomic stores of 8 bytes, for the persistent
@@ -128,6 +135,52 @@ __device__ __forceinline__ const RenderArgs &render_args(const RenderArgs &param
 #endif
 }
 
+// One exact tile whose rays are split over F.xparts adjacent lanes
+// (exact_tile_dims).  The parts are walked from full transmittance and
+// combined in ray order.  Where a ray terminates inside a part, that part is
+// walked again on top of the parts before it, so that it stops where the whole
+// ray stops; the parts behind it are left out.
+template <int FMT, int SEARCH, bool ESS, typename Idx, bool WT = false>
+__device__ __forceinline__ void split_tile(const DevVDI &V, const Frame &F, const float *s_gz, int tile_index)
+{
+    const int parts = F.xparts;
+    int tw, th, x0, y0;
+    exact_tile_dims(parts, tw, th);
+    const bool meets = place_tile(F, tw, th, VDI_BAND_ROWS / th, tile_index, x0, y0);
+    const int lane = (int)threadIdx.x, ray = lane / parts, part = lane % parts;
+    const int px = x0 + ray % tw, py = y0 + ray / tw;
+    const bool in = px < F.W && py < F.H;
+    Accum a = {0.0f, 0.0f, 0.0f, 1.0f};
+    bool own = in && part == parts - 1;  // this lane ends up with the ray's result
+    if (meets) {
+        Counters cnt = {0, 0};
+        bool walk = in;
+#pragma nounroll
+        for (int round = 0;; ++round) {
+            if (walk) trace_exact_part<FMT, SEARCH, ESS, false, Idx>(V, F, s_gz, px, py, part, parts, a, cnt);
+            if (round == 1) break;
+            Accum pre = {0.0f, 0.0f, 0.0f, 1.0f};
+            for (int k = 0; k < parts - 1; ++k) {
+                const int from = lane - part + k;
+                const Accum b = {__shfl(a.r, from), __shfl(a.g, from), __shfl(a.b, from), __shfl(a.T, from)};
+                if (k < part) append(pre, b);
+            }
+            // The ray ends inside this part (part 0 has stopped there by itself).
+            walk = in && part > 0 && pre.T > kTTerm && pre.T * a.T <= kTTerm;
+            const unsigned long long ends = (__ballot(walk) >> (lane - part)) & ((1ull << parts) - 1);
+            if (walk) {
+                a = pre;
+            } else if (own) {
+                append(pre, a);
+                a = pre;
+            }
+            own = walk || (own && ends == 0);
+            if (!__any(walk)) break;
+        }
+    }
+    if (own) store_px<WT>(&F.out[(uint64_t)py * F.W + px], to_rgba(a));
+}
+
 template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx>
 __global__ __launch_bounds__(kBlock) VDI_EXACT_OCC void k_render_exact(RenderArgs args)
 {
@@ -185,6 +238,21 @@ __device__ __forceinline__ void preview_tile(const DevVDI &V, const Frame &F, co
     }
 }
 
+// Split frames are small, and last as long as their longest part: registers
+// before wavefronts.
+#define VDI_SPLIT_OCC __attribute__((amdgpu_waves_per_eu(4)))
+template <int FMT, int SEARCH, bool ESS, typename Idx>
+__global__ __launch_bounds__(kBlock) VDI_SPLIT_OCC void k_render_split(RenderArgs args)
+{
+    const RenderArgs &A = render_args(args);
+    __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
+    if constexpr (ESS) {
+        for (int i = threadIdx.x; i <= A.V.gnz; i += kBlock) s_gz[i] = A.V.gz[i];
+        __syncthreads();
+    }
+    split_tile<FMT, SEARCH, ESS, Idx>(A.V, A.F, s_gz, (int)blockIdx.x);
+}
+
 template <int FMT, bool COUNT, typename Idx>
 __global__ __launch_bounds__(kBlock) void k_render_preview(RenderArgs args)
 {
@@ -215,7 +283,7 @@ __device__ __forceinline__ const J &job_of(const J *__restrict__ jobs, int njobs
     return jobs[lo];
 }
 
-template <int FMT, bool PREVIEW, typename Idx>
+template <int FMT, JobKind KIND, typename Idx>
 __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, int njobs)
 {
     __shared__ float s_gz[VDI_MAX_GRID_NZ + 1];
@@ -224,7 +292,9 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
     if (local >= J.ntiles) return;  // padding block: the whole workgroup leaves
     for (int i = threadIdx.x; i <= J.V.gnz; i += kBlock) s_gz[i] = J.V.gz[i];
     __syncthreads();
-    if constexpr (PREVIEW) {
+    if constexpr (KIND == kSplitJob) {
+        split_tile<FMT, VDI_SEARCH_WINDOW, true, Idx>(J.V, J.F, s_gz, (int)local);
+    } else if constexpr (KIND == kPreviewJob) {
         preview_tile<FMT, Idx>(J.V, J.F, s_gz, (int)local);
     } else {
         exact_tile<FMT, VDI_SEARCH_WINDOW, true, Idx>(J.V, J.F, s_gz, (int)local);
@@ -236,14 +306,19 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
 // to 80 VGPRs the preview loop spilled, and the benchmark step took
 // 9.95-10.09 ms against 9.74-9.83 ms.
 template <int FMT, typename Idx>
-__global__ __launch_bounds__(kBlock) VDI_EXACT_OCC void k_render_batch(const BatchJob *__restrict__ jobs, int njobs)
+__global__ __launch_bounds__(kBlock) VDI_BATCH_OCC void k_render_batch(const BatchJob *__restrict__ jobs, int njobs)
 {
-    batch_tile<FMT, false, Idx>(jobs, njobs);
+    batch_tile<FMT, kExactJob, Idx>(jobs, njobs);
+}
+template <int FMT, typename Idx>
+__global__ __launch_bounds__(kBlock) VDI_SPLIT_OCC void k_render_batch_split(const BatchJob *__restrict__ jobs, int njobs)
+{
+    batch_tile<FMT, kSplitJob, Idx>(jobs, njobs);
 }
 template <int FMT, typename Idx>
 __global__ __launch_bounds__(kBlock) void k_render_batch_preview(const BatchJob *__restrict__ jobs, int njobs)
 {
-    batch_tile<FMT, true, Idx>(jobs, njobs);
+    batch_tile<FMT, kPreviewJob, Idx>(jobs, njobs);
 }
 
 __global__ __launch_bounds__(256) void k_upsample_batch(const UpsampleJob *__restrict__ jobs, int njobs)
@@ -417,7 +492,10 @@ __global__ __launch_bounds__(kBlock) VDI_PERSIST_OCC void k_persist(const PHost 
             if (J.preview) {
                 preview_tile<FMT, uint64_t, false, true>(J.R.V, J.R.F, s_gz, (int)local);
             } else {
-                exact_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
+                if (J.R.F.xparts > 1)
+                    split_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
+                else
+                    exact_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
             }
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores have completed
             __syncthreads();                // and s_gz is free for the next tile
@@ -657,6 +735,23 @@ hipError_t launch_exact_fmt(const DevVDI &v, const Frame &f, dim3 grid, hipStrea
     default:
         if (!ess) k = k_render_exact<FMT, VDI_SEARCH_SEEDED, false, COUNT, Idx>;
     }
+    if constexpr (!COUNT)
+        if (f.xparts > 1) {
+            k = k_render_split<FMT, VDI_SEARCH_SEEDED, true, Idx>;
+            switch (f.search) {
+            case VDI_SEARCH_BINARY:
+                k = ess ? k_render_split<FMT, VDI_SEARCH_BINARY, true, Idx> : k_render_split<FMT, VDI_SEARCH_BINARY, false, Idx>;
+                break;
+            case VDI_SEARCH_LINEAR:
+                k = ess ? k_render_split<FMT, VDI_SEARCH_LINEAR, true, Idx> : k_render_split<FMT, VDI_SEARCH_LINEAR, false, Idx>;
+                break;
+            case VDI_SEARCH_WINDOW:
+                k = ess ? k_render_split<FMT, VDI_SEARCH_WINDOW, true, Idx> : k_render_split<FMT, VDI_SEARCH_WINDOW, false, Idx>;
+                break;
+            default:
+                if (!ess) k = k_render_split<FMT, VDI_SEARCH_SEEDED, false, Idx>;
+            }
+        }
     k<<<grid, kBlock, 0, s>>>(RenderArgs{v, f});
     return hipGetLastError();
 }
@@ -670,20 +765,18 @@ hipError_t launch_exact_of(const DevVDI &v, const Frame &f, bool counters, dim3 
     if (f.search != VDI_SEARCH_WINDOW || !fits32(v.WO, v.HO, v.NS)) return launch_exact_fmt<FMT, false, uint64_t>(v, f, grid, s);
     auto k = f.ess ? k_render_exact<FMT, VDI_SEARCH_WINDOW, true, false, uint32_t>
                    : k_render_exact<FMT, VDI_SEARCH_WINDOW, false, false, uint32_t>;
+    if (f.xparts > 1)
+        k = f.ess ? k_render_split<FMT, VDI_SEARCH_WINDOW, true, uint32_t> : k_render_split<FMT, VDI_SEARCH_WINDOW, false, uint32_t>;
     k<<<grid, kBlock, 0, s>>>(RenderArgs{v, f});
     return hipGetLastError();
 }
 
-inline dim3 tile_grid(int W, int H)
-{
-    return dim3((unsigned)(((W + kXTileW - 1) / kXTileW) * ((H + kXTileH - 1) / kXTileH)));
-}
 
 }  // namespace
 
 hipError_t launch_render_exact(const DevVDI &v, const Frame &f, bool counters, hipStream_t s)
 {
-    const dim3 g = tile_grid(f.W, f.H);
+    const dim3 g(exact_tiles(f.W, f.H, counters ? 1 : f.xparts));
     switch (v.fmt) {
     case VDI_F16: return launch_exact_of<VDI_F16>(v, f, counters, g, s);
     case VDI_BF16: return launch_exact_of<VDI_BF16>(v, f, counters, g, s);
@@ -719,22 +812,23 @@ hipError_t launch_upsample(const float4 *lo, int32_t w, int32_t h, float4 *out, 
 }
 
 template <int FMT>
-hipError_t launch_batch_of(const BatchJob *jobs, int32_t njobs, dim3 grid, bool preview, bool wide, hipStream_t s)
+hipError_t launch_batch_of(const BatchJob *jobs, int32_t njobs, dim3 grid, JobKind kind, bool wide, hipStream_t s)
 {
-    auto k = wide ? (preview ? k_render_batch_preview<FMT, uint64_t> : k_render_batch<FMT, uint64_t>)
-                  : (preview ? k_render_batch_preview<FMT, uint32_t> : k_render_batch<FMT, uint32_t>);
+    auto k = wide ? k_render_batch<FMT, uint64_t> : k_render_batch<FMT, uint32_t>;
+    if (kind == kSplitJob) k = wide ? k_render_batch_split<FMT, uint64_t> : k_render_batch_split<FMT, uint32_t>;
+    if (kind == kPreviewJob) k = wide ? k_render_batch_preview<FMT, uint64_t> : k_render_batch_preview<FMT, uint32_t>;
     k<<<grid, kBlock, 0, s>>>(jobs, njobs);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, bool preview, bool wide,
+hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, JobKind kind, bool wide,
                                hipStream_t s)
 {
     const dim3 g(nblocks);
     switch (fmt) {
-    case VDI_F16: return launch_batch_of<VDI_F16>(jobs, njobs, g, preview, wide, s);
-    case VDI_BF16: return launch_batch_of<VDI_BF16>(jobs, njobs, g, preview, wide, s);
-    default: return launch_batch_of<VDI_F32>(jobs, njobs, g, preview, wide, s);
+    case VDI_F16: return launch_batch_of<VDI_F16>(jobs, njobs, g, kind, wide, s);
+    case VDI_BF16: return launch_batch_of<VDI_BF16>(jobs, njobs, g, kind, wide, s);
+    default: return launch_batch_of<VDI_F32>(jobs, njobs, g, kind, wide, s);
     }
 }
 

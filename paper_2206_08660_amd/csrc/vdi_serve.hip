@@ -125,11 +125,6 @@ struct Persist {
     std::chrono::steady_clock::time_point idle_since;
 };
 
-// Workgroups of an exact render of w x h rays.
-uint32_t exact_tiles(int w, int h)
-{
-    return (uint32_t)(((w + kXTileW - 1) / kXTileW) * ((h + kXTileH - 1) / kXTileH));
-}
 // Workgroups of 256 threads upsampling a W x H image (64 x 4 pixels each).
 uint32_t upsample_tiles(int W, int H) { return (uint32_t)(((W + 63) / 64) * ((H + 3) / 4)); }
 // Job starts are multiples of the XCD count.
@@ -187,18 +182,18 @@ void launch_batch(vdi_server_s *s, Lane &L)
         take.push_back(s->queue.front());
         s->queue.pop_front();
     }
-    // Job tables: one group per (mode, format), each sorted by tile0.
+    // Job tables: one group per (kind, format), each sorted by tile0.
     int nj = 0, nu = 0;
-    int group_start[2][3], group_count[2][3];
-    uint32_t group_blocks[2][3];
+    int group_start[kJobKinds][3], group_count[kJobKinds][3];
+    uint32_t group_blocks[kJobKinds][3];
     bool wide = false;
-    for (int p = 0; p < 2; ++p)
+    for (int p = 0; p < kJobKinds; ++p)
         for (int f = 0; f < 3; ++f) {
             group_start[p][f] = nj;
             uint64_t t = 0;
             for (uint64_t tk : take) {
                 Request &r = s->requests.at(tk);
-                if (r.preview != (p == 1) || r.fmt != f) continue;
+                if (job_kind(r.preview, r.job.F) != p || r.fmt != f) continue;
                 t = align_up(t);
                 r.job.tile0 = (uint32_t)t;
                 t += r.job.ntiles;
@@ -220,11 +215,11 @@ void launch_batch(vdi_server_s *s, Lane &L)
     hipError_t e = hipMemcpyAsync(L.d_jobs, L.h_jobs, sizeof(BatchJob) * nj, hipMemcpyHostToDevice, L.stream);
     if (e == hipSuccess && nu)
         e = hipMemcpyAsync(L.d_up, L.h_up, sizeof(UpsampleJob) * nu, hipMemcpyHostToDevice, L.stream);
-    for (int p = 0; p < 2 && e == hipSuccess; ++p)
+    for (int p = 0; p < kJobKinds && e == hipSuccess; ++p)
         for (int f = 0; f < 3 && e == hipSuccess; ++f)
             if (group_count[p][f])
-                e = launch_batch_render(L.d_jobs + group_start[p][f], group_count[p][f], group_blocks[p][f], f, p == 1,
-                                        wide, L.stream);
+                e = launch_batch_render(L.d_jobs + group_start[p][f], group_count[p][f], group_blocks[p][f], f,
+                                        (JobKind)p, wide, L.stream);
     if (e == hipSuccess && nu) e = launch_batch_upsample(L.d_up, nu, (uint32_t)tu, L.stream);
     if (e == hipSuccess) e = hipEventRecord(L.done, L.stream);
     L.tickets = std::move(take);
@@ -596,7 +591,7 @@ int submit(vdi_server_t s, vdi_t v, const vdi_camera *cam, int32_t W, int32_t H,
     r.job.F.ess = 1;
     r.job.F.search = VDI_SEARCH_WINDOW;
     r.job.tile0 = 0;
-    r.job.ntiles = D_R > 0.0f ? vdi::preview_tiles(w, h) : vdi::exact_tiles(w, h);
+    r.job.ntiles = D_R > 0.0f ? vdi::preview_tiles(w, h) : vdi::exact_tiles(w, h, r.job.F.xparts);
     r.fmt = S.dev.fmt;
     r.preview = D_R > 0.0f;
     r.down = down;
@@ -701,7 +696,7 @@ struct Launch {
     int start, count;
     uint32_t nblocks;
     int fmt;
-    bool preview;
+    JobKind kind;
 };
 
 int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int32_t *widths, const int32_t *heights,
@@ -734,7 +729,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         it.fmt = S.dev.fmt;
         it.preview = D_R[i] > 0.0f;
         it.down = (w != widths[i] || h != heights[i]);
-        it.job.ntiles = it.preview ? preview_tiles(w, h) : exact_tiles(w, h);
+        it.job.ntiles = it.preview ? preview_tiles(w, h) : exact_tiles(w, h, it.job.F.xparts);
         if (it.down) {
             // Rounded up to a power of two (at least 1 MiB), as for vdi_render.
             it.lo_bytes = (size_t)1 << 20;
@@ -785,7 +780,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         release();
         return hip_error(e, "pinned job tables");
     }
-    // Job tables: one group per (mode, format), cut into launches of at most
+    // Job tables: one group per (kind, format), cut into launches of at most
     // kLaunchBlocks blocks; a job starts at a multiple of the XCD count.
     std::vector<Launch> launches, up_launches;
     {
@@ -794,14 +789,14 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         R->next = (k + 1) % kRingSlots;
         e = hipEventSynchronize(R->copied[k]);
         int nj = 0, nu = 0;
-        for (int p = 0; p < 2 && e == hipSuccess; ++p)
+        for (int p = 0; p < kJobKinds && e == hipSuccess; ++p)
             for (int f = 0; f < 3; ++f) {
                 uint64_t t = 0;
                 int start = nj;
                 for (const BatchItem &it : items) {
-                    if (it.preview != (p == 1) || it.fmt != f) continue;
+                    if (job_kind(it.preview, it.job.F) != p || it.fmt != f) continue;
                     if (nj > start && align_up(t) + it.job.ntiles > kLaunchBlocks) {
-                        launches.push_back({start, nj - start, (uint32_t)t, f, p == 1});
+                        launches.push_back({start, nj - start, (uint32_t)t, f, (JobKind)p});
                         start = nj;
                         t = 0;
                     }
@@ -811,14 +806,14 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
                     t += it.job.ntiles;
                     ++nj;
                 }
-                if (nj > start) launches.push_back({start, nj - start, (uint32_t)t, f, p == 1});
+                if (nj > start) launches.push_back({start, nj - start, (uint32_t)t, f, (JobKind)p});
             }
         uint64_t tu = 0;
         int ustart = 0;
         for (const BatchItem &it : items) {
             if (!it.down) continue;
             if (nu > ustart && align_up(tu) + it.up.ntiles > kLaunchBlocks) {
-                up_launches.push_back({ustart, nu - ustart, (uint32_t)tu, 0, false});
+                up_launches.push_back({ustart, nu - ustart, (uint32_t)tu, 0, kPreviewJob});
                 ustart = nu;
                 tu = 0;
             }
@@ -828,7 +823,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
             tu += it.up.ntiles;
             ++nu;
         }
-        if (nu > ustart) up_launches.push_back({ustart, nu - ustart, (uint32_t)tu, 0, false});
+        if (nu > ustart) up_launches.push_back({ustart, nu - ustart, (uint32_t)tu, 0, kPreviewJob});
         if (e == hipSuccess) e = hipMemcpyAsync(d_jobs, R->jobs[k], sizeof(BatchJob) * nj, hipMemcpyHostToDevice, st);
         if (e == hipSuccess && nu)
             e = hipMemcpyAsync(d_up, R->up[k], sizeof(UpsampleJob) * nu, hipMemcpyHostToDevice, st);
@@ -836,7 +831,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
     }
     for (const Launch &L : launches) {
         if (e != hipSuccess) break;
-        e = launch_batch_render(d_jobs + L.start, L.count, L.nblocks, L.fmt, L.preview, wide, st);
+        e = launch_batch_render(d_jobs + L.start, L.count, L.nblocks, L.fmt, L.kind, wide, st);
     }
     for (const Launch &L : up_launches) {
         if (e != hipSuccess) break;

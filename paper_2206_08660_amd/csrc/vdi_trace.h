@@ -747,18 +747,33 @@ VDI_HD inline bool cell_occupied(const DevVDI &V, int cell)
 // ---------------------------------------------------------------------------
 // Exact render (Sections 4.1-4.3)
 // ---------------------------------------------------------------------------
-// One exact ray through V_N pixel (px, py); s_gz = slice boundaries (LDS copy).
+// Part `part` of `parts` of the exact ray through V_N pixel (px, py),
+// composited onto A, which the caller sets to the parts before it or to full
+// transmittance; s_gz = slice boundaries (LDS copy).
 // The ray steps through the list grid (voxel stepping in V_O NDC, Section
 // 4.1), fetching the count of the list it enters next while it composites the
 // current one; with ESS on it crosses grid cells of count 0 in one step
 // (Section 4.3), keeping the current cell and depth slice from step to step.
+//
+// The parts cut [t0, t1] where the ray's position in V_O's NDC (X/Z and Y/Z,
+// linear in k) has covered k / parts of its way, which deals its list
+// crossings out evenly.  A cut lies inside a list: the pieces of a
+// supersegment on both sides of it composite to the whole piece's colour and
+// opacity (Eq. 2 is multiplicative in the length), so the parts, combined in
+// ray order, give the whole ray up to rounding.
 template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx = uint64_t>
-VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, int px, int py, Counters &cnt)
+VDI_HDI void trace_exact_part(const DevVDI &V, const Frame &F, const float *s_gz, int px, int py, int part, int parts,
+                              Accum &A, Counters &cnt)
 {
-    Accum A = {0.0f, 0.0f, 0.0f, 1.0f};
     Ray r;
     const double xc = pixel_ndc(px, F.W, F.inv_w), yc = pixel_ndc(py, F.H, F.inv_h);
-    if (!ray_setup(F, xc, yc, r)) return make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (!ray_setup(F, xc, yc, r)) return;
+    if (parts > 1) {
+        const double z0 = F.Z0 + r.t0 * r.Zp, z1 = F.Z0 + r.t1 * r.Zp, t0 = r.t0, span = r.t1 - r.t0;
+        auto cut = [&](int k) { return t0 + span * ((k * z0) * rcp64(parts * z1 - k * (z1 - z0))); };
+        if (part > 0) r.t0 = cut(part);
+        if (part + 1 < parts) r.t1 = cut(part + 1);
+    }
     const int WO = V.WO, HO = V.HO, gk = V.gk;
     // Direction of travel across the list grid: d/dt (X/Z) has the sign of Kx.
     const double Kx = r.Xp * F.Z0 - F.X0 * r.Zp, Ky = r.Yp * F.Z0 - F.Y0 * r.Zp;
@@ -899,7 +914,17 @@ VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, i
         n = n_next;
         t = fmax(t, tn);
     }
-    return make_float4(A.r, A.g, A.b, 1.0f - A.T);
+}
+
+VDI_HD inline float4 to_rgba(const Accum &A) { return make_float4(A.r, A.g, A.b, 1.0f - A.T); }
+
+// The whole exact ray.
+template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx = uint64_t>
+VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, int px, int py, Counters &cnt)
+{
+    Accum A = {0.0f, 0.0f, 0.0f, 1.0f};
+    trace_exact_part<FMT, SEARCH, ESS, COUNT, Idx>(V, F, s_gz, px, py, 0, 1, A, cnt);
+    return to_rgba(A);
 }
 
 // ---------------------------------------------------------------------------
@@ -1198,6 +1223,13 @@ VDI_HD inline Accum over(const Accum &f, const Accum &b)
     return {fmaf(f.T, b.r, f.r), fmaf(f.T, b.g, f.g), fmaf(f.T, b.b, f.b), f.T * b.T};
 }
 
+// `pre`, the parts of a ray so far in ray order, with the next one, unless the
+// ray has terminated.
+VDI_HD inline void append(Accum &pre, const Accum &a)
+{
+    if (pre.T > kTTerm) pre = over(pre, a);
+}
+
 // Combine the partial results of the `parts` lanes of each ray (adjacent
 // lanes, part = lane % parts, parts a power of two) in ray order: pairs, then
 // pairs of pairs.  Every lane of the group ends with the same result.
@@ -1209,9 +1241,6 @@ __device__ inline Accum combine_parts(Accum a, int parts, int lane)
     }
     return a;
 }
-
-VDI_HD inline float4 to_rgba(const Accum &A) { return make_float4(A.r, A.g, A.b, 1.0f - A.T); }
-
 
 // ---------------------------------------------------------------------------
 // Bilinear upsampling of one output pixel (x, y) of a W x H image from a
