@@ -89,12 +89,10 @@ int make_basis(const vdi_camera &c, Basis &b)
 
 double dot(const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
 
-// The most lists that 3 x 3 rays over the AABB's part of the image cross (where
-// exact_parts asks).
+// The most lists that 3 x 3 rays over the AABB's part of the image cross.
 double lists_crossed(const vdi::DevVDI &V, const vdi::Frame &f)
 {
     double most = 0.0;
-    if ((double)f.W * f.H > VDI_EXACT_LANES) return most;
     for (int i = 0; i < 9; ++i) {
         const double px = f.rx0 + (f.rx1 - f.rx0) * (0.1 + 0.4 * (i % 3)), py = f.ry0 + (f.ry1 - f.ry0) * (0.1 + 0.4 * (i / 3));
         vdi::Ray r;
@@ -172,7 +170,8 @@ int build_frame(const vdi::VdiSet &S, const vdi_camera &cam, int w, int h, doubl
     f.ess = 1;
     f.search = VDI_SEARCH_WINDOW;
     f.parts = vdi::preview_parts(w, h);
-    f.xparts = vdi::exact_parts(w, h, lists_crossed(S.dev, f));
+    f.lists = lists_crossed(S.dev, f);
+    f.xparts = vdi::exact_parts(w, h, f.lists);
     return VDI_OK;
 }
 

@@ -194,6 +194,7 @@ struct Frame {
     double DR;                 // > 0: along-ray subsampling
     int32_t parts;             // preview: lanes per ray (preview_parts)
     int32_t xparts;            // exact: lanes per ray (exact_parts)
+    double lists;              // about the most lists that a ray crosses
     float4 *out;               // [H][W]
     // counters (instrumented kernels only)
     uint8_t *touched_lists, *touched_slots, *touched_cells;
@@ -369,8 +370,9 @@ hipError_t launch_set_gz(const float *z, int32_t n, float *gz, hipStream_t strea
 // tile0, all of colour format fmt; nblocks covers the last job's tiles.
 // Exact jobs use the window search with empty-space skipping.  wide: some
 // job's VDI does not fit 32-bit offsets (fits32).
-// Kinds of jobs, each with a kernel of its own.
-enum JobKind { kExactJob, kSplitJob, kPreviewJob, kJobKinds };
+// Kinds of jobs, each with a kernel of its own, and the kernel that renders
+// all of them in one launch.
+enum JobKind { kExactJob, kSplitJob, kPreviewJob, kJobKinds, kMixedJobs = kJobKinds };
 inline JobKind job_kind(bool preview, const Frame &f) { return preview ? kPreviewJob : (f.xparts > 1 ? kSplitJob : kExactJob); }
 hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, JobKind kind,
                                bool wide, hipStream_t stream);

@@ -182,27 +182,35 @@ void launch_batch(vdi_server_s *s, Lane &L)
         take.push_back(s->queue.front());
         s->queue.pop_front();
     }
-    // Job tables: one group per (kind, format), each sorted by tile0.
+    // Job tables: one group per format, exact frames before previews, each
+    // sorted by tile0.
     int nj = 0, nu = 0;
-    int group_start[kJobKinds][3], group_count[kJobKinds][3];
-    uint32_t group_blocks[kJobKinds][3];
+    int group_start[3], group_count[3];
+    uint32_t group_blocks[3];
+    JobKind group_kind[3];
     bool wide = false;
-    for (int p = 0; p < kJobKinds; ++p)
-        for (int f = 0; f < 3; ++f) {
-            group_start[p][f] = nj;
-            uint64_t t = 0;
-            for (uint64_t tk : take) {
+    // Frames whose rays cross most lists first: a launch ends on its last ones.
+    std::vector<uint64_t> order(take);
+    std::stable_sort(order.begin(), order.end(), [&](uint64_t a, uint64_t b) {
+        return s->requests.at(a).job.F.lists > s->requests.at(b).job.F.lists;
+    });
+    for (int f = 0; f < 3; ++f) {
+        group_start[f] = nj;
+        uint64_t t = 0;
+        for (int p = 0; p < kJobKinds; ++p)
+            for (uint64_t tk : order) {
                 Request &r = s->requests.at(tk);
                 if (job_kind(r.preview, r.job.F) != p || r.fmt != f) continue;
+                group_kind[f] = nj == group_start[f] || group_kind[f] == p ? (JobKind)p : kMixedJobs;
                 t = align_up(t);
                 r.job.tile0 = (uint32_t)t;
                 t += r.job.ntiles;
                 wide = wide || !fits32(r.job.V.WO, r.job.V.HO, r.job.V.NS);
                 L.h_jobs[nj++] = r.job;
             }
-            group_count[p][f] = nj - group_start[p][f];
-            group_blocks[p][f] = (uint32_t)t;
-        }
+        group_count[f] = nj - group_start[f];
+        group_blocks[f] = (uint32_t)t;
+    }
     uint64_t tu = 0;
     for (uint64_t tk : take) {
         Request &r = s->requests.at(tk);
@@ -215,11 +223,9 @@ void launch_batch(vdi_server_s *s, Lane &L)
     hipError_t e = hipMemcpyAsync(L.d_jobs, L.h_jobs, sizeof(BatchJob) * nj, hipMemcpyHostToDevice, L.stream);
     if (e == hipSuccess && nu)
         e = hipMemcpyAsync(L.d_up, L.h_up, sizeof(UpsampleJob) * nu, hipMemcpyHostToDevice, L.stream);
-    for (int p = 0; p < kJobKinds && e == hipSuccess; ++p)
-        for (int f = 0; f < 3 && e == hipSuccess; ++f)
-            if (group_count[p][f])
-                e = launch_batch_render(L.d_jobs + group_start[p][f], group_count[p][f], group_blocks[p][f], f,
-                                        (JobKind)p, wide, L.stream);
+    for (int f = 0; f < 3 && e == hipSuccess; ++f)
+        if (group_count[f])
+            e = launch_batch_render(L.d_jobs + group_start[f], group_count[f], group_blocks[f], f, group_kind[f], wide, L.stream);
     if (e == hipSuccess && nu) e = launch_batch_upsample(L.d_up, nu, (uint32_t)tu, L.stream);
     if (e == hipSuccess) e = hipEventRecord(L.done, L.stream);
     L.tickets = std::move(take);
@@ -774,13 +780,18 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         release();
         return hip_error(e, "job tables");
     }
+    // Frames whose rays cross most lists first: a launch ends on its last ones.
+    std::vector<const BatchItem *> order;
+    for (const BatchItem &it : items) order.push_back(&it);
+    std::stable_sort(order.begin(), order.end(),
+                     [](const BatchItem *a, const BatchItem *b) { return a->job.F.lists > b->job.F.lists; });
     JobRing *R = nullptr;
     e = job_ring(device, &R);
     if (e != hipSuccess) {
         release();
         return hip_error(e, "pinned job tables");
     }
-    // Job tables: one group per (kind, format), cut into launches of at most
+    // Job tables: one group per format, exact frames before previews, cut into launches of at most
     // kLaunchBlocks blocks; a job starts at a multiple of the XCD count.
     std::vector<Launch> launches, up_launches;
     {
@@ -789,25 +800,28 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         R->next = (k + 1) % kRingSlots;
         e = hipEventSynchronize(R->copied[k]);
         int nj = 0, nu = 0;
-        for (int p = 0; p < kJobKinds && e == hipSuccess; ++p)
-            for (int f = 0; f < 3; ++f) {
-                uint64_t t = 0;
-                int start = nj;
-                for (const BatchItem &it : items) {
+        for (int f = 0; f < 3 && e == hipSuccess; ++f) {
+            uint64_t t = 0;
+            int start = nj;
+            JobKind kind = kExactJob;
+            for (int p = 0; p < kJobKinds; ++p)
+                for (const BatchItem *item : order) {
+                    const BatchItem &it = *item;
                     if (job_kind(it.preview, it.job.F) != p || it.fmt != f) continue;
                     if (nj > start && align_up(t) + it.job.ntiles > kLaunchBlocks) {
-                        launches.push_back({start, nj - start, (uint32_t)t, f, (JobKind)p});
+                        launches.push_back({start, nj - start, (uint32_t)t, f, kind});
                         start = nj;
                         t = 0;
                     }
+                    kind = nj == start || kind == p ? (JobKind)p : kMixedJobs;
                     t = align_up(t);
                     R->jobs[k][nj] = it.job;
                     R->jobs[k][nj].tile0 = (uint32_t)t;
                     t += it.job.ntiles;
                     ++nj;
                 }
-                if (nj > start) launches.push_back({start, nj - start, (uint32_t)t, f, (JobKind)p});
-            }
+            if (nj > start) launches.push_back({start, nj - start, (uint32_t)t, f, kind});
+        }
         uint64_t tu = 0;
         int ustart = 0;
         for (const BatchItem &it : items) {
