@@ -681,31 +681,41 @@ constexpr int kGenTileW = VDI_GEN_TILE_W, kGenTileH = 64 / VDI_GEN_TILE_W;
 #define VDI_GEN_WAVES 3  // wavefronts per SIMD the kernel is compiled for
 #endif
 
-// The kernel's G.tab into LDS, by one wavefront, straight from the kernel
-// arguments (G is the first): indexed through the parameter instead, the
-// whole of G would be copied to scratch memory and its fields kept in vector
-// registers.
-__device__ inline void copy_gen_tab(GenTab *to)
+// A kernel's GenParams, its first parameter, read from the kernel arguments
+// where they are used.  Through the parameter all of them are loaded at the
+// kernel's start and spilled from the scalar registers, and indexing any part
+// of it copies the whole to scratch memory.
+__device__ __forceinline__ const GenParams &gen_args(const GenParams &param)
 {
 #ifdef __HIP_DEVICE_COMPILE__
-    static_assert(sizeof(GenTab) % sizeof(double) == 0, "copied by doubles");
-    using Args = const __attribute__((address_space(4))) char;
-    using Doubles = const __attribute__((address_space(4))) double;
-    auto *from = (Doubles *)((Args *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(GenParams, tab));
-    for (int i = (int)threadIdx.x; i < (int)(sizeof(GenTab) / sizeof(double)); i += 64)
-        reinterpret_cast<double *>(to)[i] = from[i];
-    __syncthreads();
+    using Args = const __attribute__((address_space(4))) GenParams;
+    auto *p = (Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const GenParams *)p;
+#else
+    return param;
 #endif
 }
 
+// G.tab into LDS, by one wavefront.
+__device__ inline void copy_gen_tab(const GenParams &G, GenTab *to)
+{
+    static_assert(sizeof(GenTab) % sizeof(double) == 0, "copied by doubles");
+    const double *from = reinterpret_cast<const double *>(&G.tab);
+    for (int i = (int)threadIdx.x; i < (int)(sizeof(GenTab) / sizeof(double)); i += 64)
+        reinterpret_cast<double *>(to)[i] = from[i];
+    __syncthreads();
+}
+
 template <bool FITS, VoxelKind K_>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(VDI_GEN_WAVES))) void k_generate(GenParams G, unsigned *__restrict__ counter, int ntiles,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(VDI_GEN_WAVES))) void k_generate(GenParams args, unsigned *__restrict__ counter, int ntiles,
                                                  double2 *__restrict__ cache, int K, uint8_t *__restrict__ count,
                                                  float2 *__restrict__ depth, float4 *__restrict__ rgba,
                                                  double *__restrict__ gamma_out)
 {
+    const GenParams &G = gen_args(args);
     __shared__ GenTab s_tab;
-    copy_gen_tab(&s_tab);
+    copy_gen_tab(G, &s_tab);
     const int tiles_x = (G.cam.W + kGenTileW - 1) / kGenTileW;
     const SampleCache C = {cache + (size_t)blockIdx.x * K * 64 + threadIdx.x, K, 64};
     for (;;) {
@@ -801,11 +811,12 @@ __device__ __forceinline__ void dvr_pixel(const GenCam &cam, int &px, int &py)
 }
 
 template <VoxelKind K>
-__global__ __launch_bounds__(64) void k_dvr_f64(GenParams G, float4 *__restrict__ out)
+__global__ __launch_bounds__(64) void k_dvr_f64(GenParams args, float4 *__restrict__ out)
 {
 #pragma clang fp contract(off)
+    const GenParams &G = gen_args(args);
     __shared__ GenTab s_tab;
-    copy_gen_tab(&s_tab);
+    copy_gen_tab(G, &s_tab);
     int px, py;
     dvr_pixel(G.cam, px, py);
     if (px >= G.cam.W || py >= G.cam.H) return;
@@ -834,8 +845,9 @@ __global__ __launch_bounds__(64) void k_dvr_f64(GenParams G, float4 *__restrict_
 constexpr int kDvrAhead = 4;
 
 template <VoxelKind K>
-__global__ __launch_bounds__(64) void k_dvr_f32(GenParams G, float4 *__restrict__ out)
+__global__ __launch_bounds__(64) void k_dvr_f32(GenParams args, float4 *__restrict__ out)
 {
+    const GenParams &G = gen_args(args);
     int px, py;
     dvr_pixel(G.cam, px, py);
     if (px >= G.cam.W || py >= G.cam.H) return;
