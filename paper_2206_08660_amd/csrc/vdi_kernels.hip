@@ -71,7 +71,7 @@ __device__ __forceinline__ void store_px(float4 *p, float4 v)
 // list steps (1080p workload: two tiles in three; 32,000 of them take 40 us).
 // They come last.  The tiles that meet the AABB are dealt to the XCDs in bands
 // of `band` tile rows (xcd_tile).
-__device__ __forceinline__ bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &x0, int &y0)
+VDI_HDI bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &x0, int &y0)
 {
     const int tiles_x = (F.W + tw - 1) / tw, tiles_y = (F.H + th - 1) / th;
     const int cx0 = F.rx0 / tw, cx1 = (F.rx1 + tw - 1) / tw, cy0 = F.ry0 / th, cy1 = (F.ry1 + th - 1) / th;

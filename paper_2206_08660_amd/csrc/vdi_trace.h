@@ -213,6 +213,11 @@ VDI_HD inline double line_t(int m, double two_over_n, double P0, double Pp, doub
     return Z0 + t * Zp > 0.0 ? t : __builtin_huge_val();
 }
 
+// Shift, in V_O pixels, added to a preview sample's list coordinates: far
+// above the FP64 rounding of a coordinate (about 1e-12 pixel at 16384
+// lists) and far below any distance that decides a sample off a tie.
+constexpr double kTieShift = 1e-9;
+
 // Cell index of an NDC coordinate; a point exactly on a line belongs to the
 // cell the ray is moving into.
 VDI_HD inline int cell_of(double ndc, int n, int dir)
@@ -231,6 +236,17 @@ VDI_HD inline float div_odd(float x, float n, float inv)
 {
     const float q = x * inv;
     return fmaf(fmaf(-n, q, x), inv, q);
+}
+
+// The same for a split ray: a point within kTieShift of a line counts as on it.
+// A ray that runs along a line of list edges meets it there at every point up
+// to rounding, and each of its parts locates a start of its own: all take the
+// same side, as a ray located once does.
+VDI_HD inline int cell_of_split(double ndc, int n, int dir)
+{
+    const double f = (ndc + 1.0) * n / 2.0, m = rint(f);
+    const int i = fabs(f - m) < kTieShift ? (int)m - (dir < 0 ? 1 : 0) : (int)floor(f);
+    return min(max(i, 0), n - 1);
 }
 
 // cos of the angle between list (ix, iy)'s generating ray and V_O's axis.
@@ -795,8 +811,9 @@ VDI_HDI void trace_exact_part(const DevVDI &V, const Frame &F, const float *s_gz
     auto locate = [&](double tt) {
         const double z = F.Z0 + tt * r.Zp;
         const double iz = rcp64(z);
-        ix = cell_of((F.X0 + tt * r.Xp) * iz, WO, sx);
-        iy = cell_of((F.Y0 + tt * r.Yp) * iz, HO, sy);
+        const double x = (F.X0 + tt * r.Xp) * iz, y = (F.Y0 + tt * r.Yp) * iz;
+        ix = parts > 1 ? cell_of_split(x, WO, sx) : cell_of(x, WO, sx);
+        iy = parts > 1 ? cell_of_split(y, HO, sy) : cell_of(y, HO, sy);
         const int mx = ix + ox, my = iy + oy;
         tx = (sx != 0 && mx > 0 && mx < WO) ? line_t(mx, V.dcx, F.X0, r.Xp, F.Z0, r.Zp) : inf;
         ty = (sy != 0 && my > 0 && my < HO) ? line_t(my, V.dcy, F.Y0, r.Yp, F.Z0, r.Zp) : inf;
@@ -930,11 +947,6 @@ VDI_HDI float4 trace_exact(const DevVDI &V, const Frame &F, const float *s_gz, i
 // ---------------------------------------------------------------------------
 // Preview: adaptive along-ray subsampling (Section 4.4)
 // ---------------------------------------------------------------------------
-// Shift, in V_O pixels, added to a preview sample's list coordinates: far
-// above the FP64 rounding of a coordinate (about 1e-12 pixel at 16384
-// lists) and far below any distance that decides a sample off a tie.
-constexpr double kTieShift = 1e-9;
-
 // Part `part` of `parts` of the preview ray through V_N pixel (px, py) of
 // the (low-res) grid: the samples of a contiguous block of the grid cells the
 // ray crosses, composited front to back from full transmittance.  The blocks
