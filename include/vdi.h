@@ -91,9 +91,9 @@ typedef struct {
  *   validate  non-zero: check every list (f < b, sorted, non-overlapping,
  *           count <= N_S, opacity in [0, 1], finite values) before upload.
  *   planes_on_device  0: count, depth and rgba are host arrays.  1: they are
- *           device arrays in the same layout (vdi_generate's output), copied
- *           device to device; only the count plane is read back to the host
- *           for the checks; validate must be 0.  grid_z stays a host array.
+ *           device arrays in the same layout (vdi_generate's output), read where
+ *           they lie, the counts checked there; validate must be 0.  grid_z
+ *           stays a host array.
  * Slots at index >= count of their list are ignored.
  */
 typedef struct {
@@ -120,7 +120,7 @@ typedef struct {
 typedef struct {
     int32_t width, height, max_supersegments, rgba_fmt;
     int32_t grid_k, grid_nz, grid_w, grid_h;
-    uint64_t device_bytes; /* count + depth + colour planes + grid and its occupancy bits (twice, plus staging, once a replacement was made) */
+    uint64_t device_bytes; /* count + depth + colour planes + grid and its occupancy bits (twice, once a replacement was made, and its staging if it came from host planes) */
     uint64_t supersegments; /* sum of count */
 } vdi_info_t;
 
@@ -169,10 +169,11 @@ int vdi_render(vdi_t v, const vdi_camera *cam_VN, int32_t width, int32_t height,
  * Render n frames in one call, frame i being what vdi_render(vdis[i],
  * &cams[i], widths[i], heights[i], D_I[i], D_R[i], outs[i], hip_stream)
  * would write, bit for bit (Section 4; Eq. 2; Section 4.4).  The frames are
- * independent: instead of one launch per frame, the tiles of all exact
- * frames of one colour format form one launch, those of all preview frames
- * another, and the upsampling of all downsampled frames a third, so the long
- * rays at the end of one frame run beside the next frame's tiles.  Frames may
+ * independent: instead of one launch per frame, the tiles of all frames of
+ * one colour format form one launch, exact before preview frames and those
+ * whose rays cross most lists first, and the upsampling of all downsampled
+ * frames another, so the long rays of one frame run beside the tiles of the
+ * others.  Frames may
  * name different VDIs, all resident on the device of hip_stream.
  *   n              1 .. VDI_BATCH_MAX_FRAMES.
  *   vdis, cams, widths, heights, D_I, D_R, outs
@@ -459,9 +460,9 @@ int vdi_image_quality(const float *image, const float *reference, int32_t width,
  * one batch as soon as one of the server's streams is free: by the
  * submitting thread within vdi_server_submit if a stream is free then,
  * otherwise by a scheduler thread owned by the server.  One kernel launch
- * per (mode, colour format) group covers
- * the tiles of all the group's requests, whatever their resolution,
- * viewpoint and preview level, and one more upsamples those with D_I > 1.
+ * per colour format covers the tiles of all its requests, whatever their mode,
+ * resolution, viewpoint and preview level, and one more upsamples those with
+ * D_I > 1.
  * With two or more streams the next batches start while earlier ones
  * drain.  A request is done when its batch is.  A request's image is
  * identical to vdi_render's with the same arguments.

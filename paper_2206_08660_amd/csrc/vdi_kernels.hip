@@ -13,7 +13,8 @@
 // The planes are stored in bricks of 2 x 2 neighbouring lists (see
 // list_base_xy), so one 128-byte line holds several slots of the lists a
 // tile column reads together, and lists revisited by neighbouring rays are
-// served from L1/L2 (the paper's spatial smoothness).  Preview wavefronts
+// served from L1/L2 (the paper's spatial smoothness).  Rays of small exact
+// frames are split over up to 16 lanes (exact_parts).  Preview wavefronts
 // cover 64 x 1 tiles of the low-res grid, split by lanes per ray.  Tiles are
 // dealt to the 8 XCDs in interleaved bands of rows (xcd_tile), so
 // neighbouring tiles share an L2 and every XCD gets part of the image
@@ -71,13 +72,13 @@ __device__ __forceinline__ void store_px(float4 *p, float4 v)
 // list steps (1080p workload: two tiles in three; 32,000 of them take 40 us).
 // They come last.  The tiles that meet the AABB are dealt to the XCDs in bands
 // of `band` tile rows (xcd_tile).
-VDI_HDI bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &x0, int &y0)
+VDI_HDI bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &x0, int &y0, bool middle_out = false)
 {
     const int tiles_x = (F.W + tw - 1) / tw, tiles_y = (F.H + th - 1) / th;
     const int cx0 = F.rx0 / tw, cx1 = (F.rx1 + tw - 1) / tw, cy0 = F.ry0 / th, cy1 = (F.ry1 + th - 1) / th;
     const int nx = max(cx1 - cx0, 0), ny = nx > 0 ? max(cy1 - cy0, 0) : 0, inside = nx * ny;
     if (bid < inside) {
-        const int t = xcd_tile(bid, nx, ny, band);
+        const int t = xcd_tile(bid, nx, ny, band, middle_out);
         x0 = (cx0 + t % nx) * tw;
         y0 = (cy0 + t / nx) * th;
         return true;
@@ -146,7 +147,7 @@ __device__ __forceinline__ void split_tile(const DevVDI &V, const Frame &F, cons
     const int parts = F.xparts;
     int tw, th, x0, y0;
     exact_tile_dims(parts, tw, th);
-    const bool meets = place_tile(F, tw, th, VDI_BAND_ROWS / th, tile_index, x0, y0);
+    const bool meets = place_tile(F, tw, th, VDI_BAND_ROWS / th, tile_index, x0, y0, true);
     const int lane = (int)threadIdx.x, ray = lane / parts, part = lane % parts;
     const int px = x0 + ray % tw, py = y0 + ray / tw;
     const bool in = px < F.W && py < F.H;
@@ -301,10 +302,8 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
     }
 }
 
-// Exact tiles at the exact kernel's occupancy (6 wavefronts per SIMD);
-// preview tiles at the preview kernel's (its registers, 5 wavefronts): held
-// to 80 VGPRs the preview loop spilled, and the benchmark step took
-// 9.95-10.09 ms against 9.74-9.83 ms.
+// Jobs of one kind alone in a launch: exact tiles at 7 wavefronts per SIMD,
+// preview tiles at the preview kernel's registers (5 wavefronts).
 template <int FMT, typename Idx>
 __global__ __launch_bounds__(kBlock) VDI_BATCH_OCC void k_render_batch(const BatchJob *__restrict__ jobs, int njobs)
 {

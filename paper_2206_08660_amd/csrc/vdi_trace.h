@@ -69,15 +69,19 @@ VDI_HD inline double dot3(const double *a, const double *b) { return a[0] * b[0]
 // image outwards: the longest rays, which a launch ends on if they start last,
 // are more often there than at the rims (bands in image order against this:
 // 1080p f16 20 deg 635 -> 599 us, 1080p preview 209 -> 192, 720p f32 30 deg
-// 1079 -> 1053, served mix 6892 -> 6768).  The map is a bijection from
-// [0, tiles_x * tiles_y) onto itself.
+// 1079 -> 1053, served mix 6892 -> 6768).  Tiles that are all in flight at once
+// (6 wavefronts on each of 1024 SIMDs) keep the image's order: there the middle
+// first only crowds it (600 x 500, 40 deg: 1034 us, from the middle 1186),
+// unless the caller wants it (split frames, 128 x 128 at 5 deg: 31.6 -> 28.7 us).  The
+// map is a bijection from [0, tiles_x * tiles_y) onto itself.
+constexpr int kMiddleOut = 6144;
 #ifndef VDI_BAND_ROWS
 #define VDI_BAND_ROWS 8
 #endif
 constexpr int kBandRows = VDI_BAND_ROWS / kTileH > 0 ? VDI_BAND_ROWS / kTileH : 1;     // rows of 64 x 1 tiles
 constexpr int kXBandRows = VDI_BAND_ROWS / kXTileH > 0 ? VDI_BAND_ROWS / kXTileH : 1;  // rows of exact tiles
 
-VDI_HD inline int xcd_tile(int bid, int tiles_x, int tiles_y, int band_rows = kBandRows)
+VDI_HD inline int xcd_tile(int bid, int tiles_x, int tiles_y, int band_rows = kBandRows, bool middle_out = false)
 {
     const int total = tiles_x * tiles_y;
     const int x = bid % kXcds, nth = bid / kXcds;
@@ -94,6 +98,10 @@ VDI_HD inline int xcd_tile(int bid, int tiles_x, int tiles_y, int band_rows = kB
         if (nbg > 0 && (nb - 1) % kXcds == g) size -= (band_rows - last_rows) * tiles_x;
         if (pos < start + size) {
             int local = pos - start;
+            if (total <= kMiddleOut && !middle_out) {
+                const int b = g + kXcds * (local / band_tiles);
+                return b * band_tiles + local % band_tiles;
+            }
             // The group's short last band, if it has it, is visited as its
             // ks-th; what follows it starts earlier by what it lacks.
             const int ks = nbg & 1 ? nbg - 1 : nbg - 2;
