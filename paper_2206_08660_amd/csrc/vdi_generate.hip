@@ -174,7 +174,13 @@ __host__ __device__ inline int clampi(int x, int lo, int hi) { return x < lo ? l
 // bytes, aligned to a voxel only (global loads allow that); the volume is at
 // least two voxels wide.  kAny: any format and width, one voxel a load.
 enum VoxelKind { kF32, kU16, kAny };
-inline VoxelKind voxel_kind(const GenVol &v) { return v.nx < 2 ? kAny : (v.is_u16 ? kU16 : kF32); }
+// f(kind of v's voxels, as a type).
+template <typename F>
+auto by_kind(const GenVol &v, F f)
+{
+    if (v.nx < 2) return f(std::integral_constant<VoxelKind, kAny>());
+    return v.is_u16 ? f(std::integral_constant<VoxelKind, kU16>()) : f(std::integral_constant<VoxelKind, kF32>());
+}
 
 typedef uint32_t PairU16 __attribute__((aligned(2), may_alias));
 typedef uint64_t PairF32 __attribute__((aligned(4), may_alias));
@@ -1059,6 +1065,25 @@ void gcross(const double *a, const double *b, double *o)
 namespace vdi {
 namespace {
 
+// Whether a ray's parameters t may exceed 1e8 ds.  Up to there a rounding of t
+// (2^-53 of it) is about 1e-8 of a sample.
+bool eye_far(const GenParams &G)
+{
+    double d2 = 0.0;  // to the AABB's farthest corner
+    for (int a = 0; a < 3; ++a) {
+        const double d = std::max(fabs(G.vol.bmin[a] - G.cam.eye[a]), fabs(G.vol.bmax[a] - G.cam.eye[a]));
+        d2 += d * d;
+    }
+    return !(sqrt(d2) <= 1e8 * G.ds);
+}
+
+// Samples that each of `lanes` lanes caches: all that a ray can have, G.maxs
+// (sample_count), while the cache fits the budget.
+int cache_entries(const GenParams &G, size_t lanes)
+{
+    return (int)std::min<size_t>((size_t)G.maxs, kGenCacheBytes / (lanes * sizeof(double2)));
+}
+
 // Check the arguments and fill the per-call constants of the kernel.
 int make_gen_params(const vdi_volume *vol, const vdi_gen_params *p, GenParams &G)
 {
@@ -1120,6 +1145,11 @@ int make_gen_params(const vdi_volume *vol, const vdi_gen_params *p, GenParams &G
     const int nmax = std::max(vol->nx, std::max(vol->ny, vol->nz));
     G.ds = ext / nmax;  // one voxel of the longest axis
     G.maxs = 2 * nmax + 8;
+    // A ray has at most one sample per ds of the AABB's diagonal and one more
+    // (its last): less than maxs, as long as the eye is not so far away that
+    // t1 - t0 is a rounding error of t1.
+    const double diag = sqrt(G.vol.ext[0] * G.vol.ext[0] + G.vol.ext[1] * G.vol.ext[1] + G.vol.ext[2] * G.vol.ext[2]);
+    if (!eye_far(G)) G.maxs = (int)std::min((double)G.maxs, ceil(diag / G.ds) + 2.0);
     G.NS = p->max_supersegments;
     G.delta = (int)floor(0.15 * G.NS);
     G.tf = p->tf;
@@ -1148,11 +1178,8 @@ extern "C" int vdi_generate(const vdi_volume *vol, const vdi_gen_params *p, uint
     const long long ntiles = (long long)((p->width + vdi::kGenTileW - 1) / vdi::kGenTileW) *
                              ((p->height + vdi::kGenTileH - 1) / vdi::kGenTileH);
     const int blocks = (int)std::max<long long>(1, std::min<long long>(ntiles, (long long)std::max(1, cus * per_cu)));
-    // Each lane caches up to K samples: all that a ray can have (its length is
-    // at most the AABB's diagonal) while the cache fits the budget.
-    const double diag = sqrt(G.vol.ext[0] * G.vol.ext[0] + G.vol.ext[1] * G.vol.ext[1] + G.vol.ext[2] * G.vol.ext[2]);
-    const int need = (int)std::min((double)G.maxs, ceil(diag / G.ds) + 2.0);
-    const int K = (int)std::min<size_t>((size_t)need, vdi::kGenCacheBytes / ((size_t)blocks * 64 * sizeof(double2)));
+    const int K = vdi::cache_entries(G, (size_t)blocks * 64);
+    const bool fits = K == G.maxs;
     const size_t cache_bytes = (size_t)blocks * K * 64 * sizeof(double2);
     size_t bytes = (size_t)1 << 20;
     while (bytes < 256 + cache_bytes) bytes <<= 1;
@@ -1164,12 +1191,9 @@ extern "C" int vdi_generate(const vdi_volume *vol, const vdi_gen_params *p, uint
     if (e != hipSuccess) return vdi::set_error(VDI_ERR_OOM, "generation scratch (%zu bytes)", bytes);
     e = hipMemsetAsync(scratch, 0, sizeof(unsigned), st);
     if (e == hipSuccess) {
-        auto kernel = vdi::k_generate<false, vdi::kAny>;
-        switch (vdi::voxel_kind(G.vol)) {
-        case vdi::kF32: kernel = K == need ? vdi::k_generate<true, vdi::kF32> : vdi::k_generate<false, vdi::kF32>; break;
-        case vdi::kU16: kernel = K == need ? vdi::k_generate<true, vdi::kU16> : vdi::k_generate<false, vdi::kU16>; break;
-        default: break;
-        }
+        auto kernel = vdi::by_kind(G.vol, [&](auto k) {
+            return fits ? vdi::k_generate<true, decltype(k)::value> : vdi::k_generate<false, decltype(k)::value>;
+        });
         kernel<<<blocks, 64, 0, st>>>(G, reinterpret_cast<unsigned *>(scratch), (int)ntiles,
                                                reinterpret_cast<double2 *>(scratch + 256), K, count,
                                                reinterpret_cast<float2 *>(depth), reinterpret_cast<float4 *>(rgba),
@@ -1203,12 +1227,8 @@ extern "C" int vdi_dvr(const vdi_volume *vol, const vdi_dvr_params *p, float *ou
     auto *out = reinterpret_cast<float4 *>(out_rgba);
     const hipStream_t st = static_cast<hipStream_t>(stream);
     const bool f64 = p->precision == VDI_DVR_F64;
-    auto kernel = f64 ? vdi::k_dvr_f64<vdi::kAny> : vdi::k_dvr_f32<vdi::kAny>;
-    switch (vdi::voxel_kind(G.vol)) {
-    case vdi::kF32: kernel = f64 ? vdi::k_dvr_f64<vdi::kF32> : vdi::k_dvr_f32<vdi::kF32>; break;
-    case vdi::kU16: kernel = f64 ? vdi::k_dvr_f64<vdi::kU16> : vdi::k_dvr_f32<vdi::kU16>; break;
-    default: break;
-    }
+    auto kernel = vdi::by_kind(
+        G.vol, [&](auto k) { return f64 ? vdi::k_dvr_f64<decltype(k)::value> : vdi::k_dvr_f32<decltype(k)::value>; });
     kernel<<<grid, 64, 0, st>>>(G, out);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return vdi::hip_error(e, "DVR launch");
