@@ -58,7 +58,7 @@ struct GenTab {
 struct GenParams {
     GenCam cam;
     GenVol vol;
-    int NS, tf, maxs, delta;
+    int NS, tf, maxs, delta, far_eye;
     double ds, gamma;  // gamma > 0: fixed
     GenTab tab;
 };
@@ -172,14 +172,26 @@ __host__ __device__ inline int clampi(int x, int lo, int hi) { return x < lo ? l
 
 // How a kernel reads voxels.  kF32, kU16: x-neighbours in one load of 8 or 4
 // bytes, aligned to a voxel only (global loads allow that); the volume is at
-// least two voxels wide.  kAny: any format and width, one voxel a load.
-enum VoxelKind { kF32, kU16, kAny };
-// f(kind of v's voxels, as a type).
+// least two voxels wide.  kAny: any format and width, one voxel a load.  kFar:
+// as kAny, for far eyes (eye_far): there the length of a sample or of a
+// supersegment is mostly the rounding of its ends, so that a power's exponent
+// may be anything and Eq. 1 is decided in FP64 alone.
+enum VoxelKind { kF32, kU16, kAny, kFar };
+// f(kind of G's volume and eye, as a type).
 template <typename F>
-auto by_kind(const GenVol &v, F f)
+auto by_kind(const GenParams &G, F f)
 {
-    if (v.nx < 2) return f(std::integral_constant<VoxelKind, kAny>());
-    return v.is_u16 ? f(std::integral_constant<VoxelKind, kU16>()) : f(std::integral_constant<VoxelKind, kF32>());
+    if (G.far_eye) return f(std::integral_constant<VoxelKind, kFar>());
+    if (G.vol.nx < 2) return f(std::integral_constant<VoxelKind, kAny>());
+    return G.vol.is_u16 ? f(std::integral_constant<VoxelKind, kU16>()) : f(std::integral_constant<VoxelKind, kF32>());
+}
+
+// x^y by pow_tab, or for far eyes by pow.
+template <VoxelKind K, bool WIDE>
+__host__ __device__ inline double power(const GenTab &W, double x, double y)
+{
+    if constexpr (K == kFar) return pow(x, y);
+    else return pow_tab<WIDE>(W, x, y);
 }
 
 typedef uint32_t PairU16 __attribute__((aligned(2), may_alias));
@@ -195,7 +207,7 @@ __host__ __device__ __forceinline__ void load_corners(const GenVol &v, const int
     const int x0 = clampi(f[0], 0, v.nx - 1), x1 = clampi(f[0] + 1, 0, v.nx - 1);
     const int y0 = clampi(f[1], 0, v.ny - 1), y1 = clampi(f[1] + 1, 0, v.ny - 1);
     const int z0 = clampi(f[2], 0, v.nz - 1), z1 = clampi(f[2] + 1, 0, v.nz - 1);
-    const int xb = K == kAny ? 0 : clampi(f[0], 0, v.nx - 2);
+    const int xb = K == kAny || K == kFar ? 0 : clampi(f[0], 0, v.nx - 2);
     const size_t at = (size_t)(uint32_t)(z0 * v.ny + y0) * (uint32_t)v.nx + (uint32_t)xb;
     const size_t dy = y1 != y0 ? (size_t)v.nx : 0, dz = z1 != z0 ? (size_t)v.nx * v.ny : 0;
 #pragma unroll
@@ -278,7 +290,7 @@ __host__ __device__ inline Sample take_sample(const GenParams &G, const GenTab &
     Sample s;
     double atf;
     tf_eval<true>(W, G.tf, v, s.c, atf);
-    s.a = atf > 0.0 ? 1.0 - pow_tab<false>(W, 1.0 - atf, len / G.ds) : 0.0;
+    s.a = atf > 0.0 ? 1.0 - power<K, false>(W, 1.0 - atf, len / G.ds) : 0.0;
     s.v = v;
     return s;
 }
@@ -333,11 +345,12 @@ __host__ __device__ inline void take(Open &o, const Sample &s, int q)
 
 // Eq. 1's distance between the open supersegment, its opacity normalised to
 // one sample length, and the next sample, in FP64, against gamma.
+template <VoxelKind K>
 __host__ __device__ inline bool far_exact(const GenTab &W, const Open &o, const Sample &s, double t0, double len, double gamma)
 {
 #pragma clang fp contract(off)
     const double lenS = (t0 + o.qe * len) - (t0 + o.qs * len);
-    const double abar = 1.0 - pow_tab<true>(W, 1.0 - o.A, len / lenS);
+    const double abar = 1.0 - power<K, true>(W, 1.0 - o.A, len / lenS);
     double d2 = 0.0;
     for (int m = 0; m < 3; ++m) {
         const double e = o.C[m] / o.A * abar - s.c[m] * s.a;
@@ -351,7 +364,7 @@ __host__ __device__ inline bool far_exact(const GenTab &W, const Open &o, const 
 // reciprocal); only when it lies within kFarErr of gamma is far_exact asked,
 // so the outcome is always far_exact's.  The bound, for a ray whose opacities
 // are at most 0.25 and whose colours lie in [0, 1] (Passes::err is NaN
-// for others, and every decision exact): with m = qe - qs samples the
+// for others and for far eyes, and every decision exact): with m = qe - qs samples the
 // normalised opacity is 1 - 2^(log2(1 - A) / m), where |log2(1 - A) / m| <=
 // 0.42 since it is the mean of the samples' logarithms.  Rounding 1 - A to
 // FP32 moves the exponent by at most 1e-7, the logarithm's, reciprocal's and
@@ -445,7 +458,7 @@ __host__ __device__ inline void count_segments(const GenParams &G, const GenTab 
                 const Open x = {{of(o[0].C[0], o[1].C[0], o[2].C[0]), of(o[0].C[1], o[1].C[1], o[2].C[1]),
                                  of(o[0].C[2], o[1].C[2], o[2].C[2])},
                                 of(o[0].A, o[1].A, o[2].A), of(o[0].qs, o[1].qs, o[2].qs), of(o[0].qe, o[1].qe, o[2].qe)};
-                const int f = far_exact(W, x, s, P.t0, P.len, of(g[0].gamma, g[1].gamma, g[2].gamma));
+                const int f = far_exact<K>(W, x, s, P.t0, P.len, of(g[0].gamma, g[1].gamma, g[2].gamma));
                 if (k == 0) far[0] = f;
                 else if (k == 1) far[1] = f;
                 else far[2] = f;
@@ -494,7 +507,7 @@ __host__ __device__ inline int split_ray(const GenParams &G, const GenTab &W, co
         const Sample s = samples.next(G, W, C, d, P.t0, P.len, q, P.ns);
         if (o.qs >= 0 && n != cap - 1) {
             int far = s.a == 0.0 ? 1 : far_filter(o, s, g);
-            if (far < 0) far = far_exact(W, o, s, P.t0, P.len, g.gamma);
+            if (far < 0) far = far_exact<K>(W, o, s, P.t0, P.len, g.gamma);
             if (far) close();
         }
         if (s.a != 0.0) take(o, s, q);
@@ -639,7 +652,7 @@ __host__ __device__ inline void gen_ray(const GenParams &G, const GenTab &pw, co
         // each normalised opacity, a mean, no more than the largest).
         double T = 1.0, most = 0.0;
         int ns = 0, runs = 0;
-        bool plain = true, gap = true;
+        bool plain = K != kFar, gap = true;
         for (int q = 0; q < N; ++q) {
             const Sample s = take_sample<K>(G, pw, d, t0, len, q);
             if (FITS || q < C.K) C.p[(size_t)q * C.stride] = make_double2(s.v, s.a);
@@ -1149,7 +1162,8 @@ int make_gen_params(const vdi_volume *vol, const vdi_gen_params *p, GenParams &G
     // (its last): less than maxs, as long as the eye is not so far away that
     // t1 - t0 is a rounding error of t1.
     const double diag = sqrt(G.vol.ext[0] * G.vol.ext[0] + G.vol.ext[1] * G.vol.ext[1] + G.vol.ext[2] * G.vol.ext[2]);
-    if (!eye_far(G)) G.maxs = (int)std::min((double)G.maxs, ceil(diag / G.ds) + 2.0);
+    G.far_eye = eye_far(G);
+    if (!G.far_eye) G.maxs = (int)std::min((double)G.maxs, ceil(diag / G.ds) + 2.0);
     G.NS = p->max_supersegments;
     G.delta = (int)floor(0.15 * G.NS);
     G.tf = p->tf;
@@ -1191,7 +1205,7 @@ extern "C" int vdi_generate(const vdi_volume *vol, const vdi_gen_params *p, uint
     if (e != hipSuccess) return vdi::set_error(VDI_ERR_OOM, "generation scratch (%zu bytes)", bytes);
     e = hipMemsetAsync(scratch, 0, sizeof(unsigned), st);
     if (e == hipSuccess) {
-        auto kernel = vdi::by_kind(G.vol, [&](auto k) {
+        auto kernel = vdi::by_kind(G, [&](auto k) {
             return fits ? vdi::k_generate<true, decltype(k)::value> : vdi::k_generate<false, decltype(k)::value>;
         });
         kernel<<<blocks, 64, 0, st>>>(G, reinterpret_cast<unsigned *>(scratch), (int)ntiles,
@@ -1228,7 +1242,7 @@ extern "C" int vdi_dvr(const vdi_volume *vol, const vdi_dvr_params *p, float *ou
     const hipStream_t st = static_cast<hipStream_t>(stream);
     const bool f64 = p->precision == VDI_DVR_F64;
     auto kernel = vdi::by_kind(
-        G.vol, [&](auto k) { return f64 ? vdi::k_dvr_f64<decltype(k)::value> : vdi::k_dvr_f32<decltype(k)::value>; });
+        G, [&](auto k) { return f64 ? vdi::k_dvr_f64<decltype(k)::value> : vdi::k_dvr_f32<decltype(k)::value>; });
     kernel<<<grid, 64, 0, st>>>(G, out);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return vdi::hip_error(e, "DVR launch");

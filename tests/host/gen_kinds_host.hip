@@ -32,7 +32,7 @@ extern "C" int host_generate_kind(const vdi_volume *vol, const vdi_gen_params *p
     const int room = 2 * std::max(vol->nx, std::max(vol->ny, vol->nz)) + 8;
     std::vector<double2> buf((size_t)K + room);
     const vdi::SampleCache C = {buf.data(), K, 1};
-    vdi::by_kind(G.vol, [&](auto kind) {
+    vdi::by_kind(G, [&](auto kind) {
         constexpr vdi::VoxelKind k = decltype(kind)::value;
         for (int py = 0; py < p->height; ++py)
             for (int px = 0; px < p->width; ++px) {

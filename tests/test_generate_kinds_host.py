@@ -93,3 +93,18 @@ def test_samples_of_far_eyes_stay_in_the_cache(host, eye, fov, u16):
     cam = inputs.Camera(eye=(eye, eye, eye), target=(0.0, 0.0, 0.0), up=(0.0, 1.0, 0.0), fov_y_deg=fov)
     _, fits, n = check(host, vol, cam, 25, 21, 5, inputs.TF_KNOTS4, 0.02, CARD, compare=False)
     assert fits and n > 0
+
+
+@pytest.mark.parametrize("lanes", [CARD, CROWD])
+@pytest.mark.parametrize("dims,u16", [((24, 31, 40), False), ((32, 32, 32), True), ((1, 9, 40), False)])
+def test_far_eyes_match_the_cpu_generator(host, dims, u16, lanes):
+    """Down to where a sample's length and a supersegment's are their ends' rounding: powers of any exponent, and
+    distances that the FP32 filter has no bound for."""
+    vol, found = volume(dims, u16), 0
+    for eye, fov in [(2.0e4, 4e-3), (2.0e6, 4e-5), (3.0e8, 2e-7), (7.0e10, 8e-10), (1.0e13, 7e-12), (1.6e14, 4e-13),
+                     (1.5e15, 4e-14)]:
+        cam = inputs.Camera(eye=(eye, 0.9 * eye, eye), target=(0.0, 0.0, 0.0), up=(0.0, 1.0, 0.0), fov_y_deg=fov)
+        for tf, gamma in [(inputs.TF_KNOTS4, 0.0), (inputs.TF_KNOTS4, 0.02), (inputs.TF_RAMP, 0.0)]:
+            _, _, n = check(host, vol, cam, 25, 21, 5, tf, gamma, lanes)
+            found += n
+    assert found > 100
