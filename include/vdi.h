@@ -92,7 +92,8 @@ typedef struct {
  *           count <= N_S, opacity in [0, 1], finite values) before upload.
  *   planes_on_device  0: count, depth and rgba are host arrays.  1: they are
  *           device arrays in the same layout (vdi_generate's output), read where
- *           they lie, the counts checked there; validate must be 0.  grid_z
+ *           they lie if that is memory of the VDI's device, aligned to a slot,
+ *           and copied there first otherwise; validate must be 0.  grid_z
  *           stays a host array.
  * Slots at index >= count of their list are ignored.
  */
@@ -120,7 +121,7 @@ typedef struct {
 typedef struct {
     int32_t width, height, max_supersegments, rgba_fmt;
     int32_t grid_k, grid_nz, grid_w, grid_h;
-    uint64_t device_bytes; /* count + depth + colour planes + grid and its occupancy bits (twice, once a replacement was made, and its staging if it came from host planes) */
+    uint64_t device_bytes; /* count + depth + colour planes + grid and its occupancy bits (twice, once a replacement was made, and its staging if its planes were not read in place) */
     uint64_t supersegments; /* sum of count */
 } vdi_info_t;
 

@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -411,18 +412,47 @@ void free_vdi(vdi_s *v)
     delete v;
 }
 
+// Whether the upload's kernels read d's planes where they lie.
+bool planes_in_place(const vdi_desc *d, int device)
+{
+    if (!d->planes_on_device) return false;
+    const struct {
+        const void *p;
+        size_t align;
+    } planes[3] = {{d->count, 1}, {d->depth, sizeof(float2)}, {d->rgba, d->rgba_fmt_in == VDI_F32 ? sizeof(float4) : sizeof(uint2)}};
+    for (const auto &q : planes) {
+        hipPointerAttribute_t a;
+        if (hipPointerGetAttributes(&a, q.p) != hipSuccess) {
+            (void)hipGetLastError();  // not known to the runtime: no error of this call
+            return false;
+        }
+        if (!vdi::readable_in_place(a, q.p, device, q.align)) return false;
+    }
+    return true;
+}
+
 // What the upload needs to know of the counts: their sum, and that none
-// exceeds max_supersegments.  A host plane is read here; a device plane by a
-// kernel on `st`, whose few results are waited for (the plane must be complete).
-int check_counts(const vdi_desc *d, hipStream_t st, uint64_t *total)
+// exceeds max_supersegments.  A host plane, or a host copy of a device plane
+// that is not read in place, is read here; the others by a kernel on `st`, whose
+// few results are waited for (the plane must be complete).
+int check_counts(const vdi_desc *d, bool in_place, hipStream_t st, uint64_t *total)
 {
     const uint64_t plane = (uint64_t)d->width * d->height;
     uint64_t sum = 0;
     uint32_t most = 0;
-    if (!d->planes_on_device) {
+    if (!in_place) {
+        std::unique_ptr<uint8_t[]> copy;
+        const uint8_t *count = d->count;
+        if (d->planes_on_device) {
+            copy.reset(new (std::nothrow) uint8_t[plane]);
+            if (!copy) return fail(VDI_ERR_OOM, "host allocation");
+            const hipError_t e = hipMemcpy(copy.get(), d->count, plane, hipMemcpyDeviceToHost);
+            if (e != hipSuccess) return hip_fail(e, "count plane download");
+            count = copy.get();
+        }
         for (uint64_t li = 0; li < plane; ++li) {
-            sum += d->count[li];
-            most = std::max<uint32_t>(most, d->count[li]);
+            sum += count[li];
+            most = std::max<uint32_t>(most, count[li]);
         }
     } else {
         vdi::CountStats part[vdi::kCountBlocks], *d_part = nullptr;
@@ -474,7 +504,7 @@ int check_desc(const vdi_desc *d, Basis &ob, std::vector<float> &gz, uint64_t *t
     if (d->planes_on_device && d->validate)
         return fail(VDI_ERR_ARG, "list validation reads the planes on the host: not available for device planes");
     if (!d->planes_on_device) {
-        rc = check_counts(d, nullptr, total);
+        rc = check_counts(d, false, nullptr, total);
         if (rc) return rc;
     }
     if (d->validate) {
@@ -518,10 +548,10 @@ uint64_t set_bytes_of(const vdi_desc *d)
 
 // Upload d into the set S on stream st: allocate S's buffers if it has none,
 // copy the count plane and slice boundaries and scatter the slot planes into
-// storage order (colour converted on the way): device planes from where they
-// are, host planes as many whole slots at a time as `stage` (stage_bytes)
+// storage order (colour converted on the way): planes read in place from where
+// they are, others as many whole slots at a time as `stage` (stage_bytes)
 // holds; then build the count grid.  Enqueues only; the caller synchronises.
-hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, uint64_t total, const Basis &ob, const std::vector<float> &gz,
+hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, bool in_place, uint64_t total, const Basis &ob, const std::vector<float> &gz,
                       hipStream_t st, void *stage, uint64_t stage_bytes, const char **what)
 {
     const uint64_t plane = (uint64_t)d->width * d->height;
@@ -568,10 +598,13 @@ hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, uint64_t total, const B
     D.gz = S.d_gz;
     *what = "upload";
     const bool on_dev = d->planes_on_device != 0;
-    e = on_dev ? hipMemcpyAsync(S.d_count, d->count, plane, hipMemcpyDeviceToDevice, st) : h2d(S.d_count, d->count, plane, st);
+    auto copy_in = [&](void *dst, const void *src, size_t n) {
+        return on_dev ? hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToDevice, st) : h2d(dst, src, n, st);
+    };
+    e = copy_in(S.d_count, d->count, plane);
     if (e == hipSuccess) e = vdi::launch_set_gz(gz.data(), (int32_t)gz.size(), S.d_gz, st);
     const size_t colour_in = d->rgba_fmt_in == VDI_F32 ? 16 : 8;
-    const uint64_t slots = on_dev ? ns : std::max<uint64_t>(1, std::min<uint64_t>(ns, stage_bytes / (plane * 16)));
+    const uint64_t slots = in_place ? ns : std::max<uint64_t>(1, std::min<uint64_t>(ns, stage_bytes / (plane * 16)));
     for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
         const bool dep = pass == 0;
         const size_t esz = dep ? sizeof(float2) : colour_in;
@@ -580,9 +613,9 @@ hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, uint64_t total, const B
             const uint64_t nj = std::min(slots, ns - j0);
             const char *from = src + j0 * plane * esz;
             // Stream order keeps the staging buffer from being refilled before it is scattered.
-            if (!on_dev) e = h2d(stage, from, nj * plane * esz, st);
+            if (!in_place) e = copy_in(stage, from, nj * plane * esz);
             if (e == hipSuccess)
-                e = vdi::launch_scatter_slots(on_dev ? from : stage, d->rgba_fmt_in, dep ? (void *)S.d_depth : S.d_rgba,
+                e = vdi::launch_scatter_slots(in_place ? from : stage, d->rgba_fmt_in, dep ? (void *)S.d_depth : S.d_rgba,
                                               d->rgba_fmt_store, dep, (int32_t)j0, (int32_t)nj, D, st);
         }
     }
@@ -754,15 +787,16 @@ int vdi_create(const vdi_desc *d, vdi_t *out)
     // waited for the device's other work as well (measured).
     if (e == hipSuccess) what = "VDI stream", e = hipStreamCreateWithFlags(&v->copy, hipStreamNonBlocking);
     hipStream_t st = v->copy;
+    const bool in_place = planes_in_place(d, v->device);
     if (e == hipSuccess && d->planes_on_device) {
-        rc = check_counts(d, st, &total);
+        rc = check_counts(d, in_place, st, &total);
         if (rc) {
             free_vdi(v);
             return rc;
         }
     }
-    if (e == hipSuccess && !d->planes_on_device) what = "staging", e = hipMallocAsync(&stage, stage_bytes, st);
-    if (e == hipSuccess) e = upload_set(v->cur, d, total, ob, gz, st, stage, stage_bytes, &what);
+    if (e == hipSuccess && !in_place) what = "staging", e = hipMallocAsync(&stage, stage_bytes, st);
+    if (e == hipSuccess) e = upload_set(v->cur, d, in_place, total, ob, gz, st, stage, stage_bytes, &what);
     if (stage) {
         const hipError_t ef = hipFreeAsync(stage, st);
         if (e == hipSuccess) e = ef;
@@ -810,8 +844,9 @@ int vdi_replace_begin(vdi_t v, const vdi_desc *d, void *stream)
     const uint64_t plane = (uint64_t)d->width * d->height;
     const char *what = "replacement set-up";
     hipError_t e = hipSetDevice(v->device);
+    const bool in_place = planes_in_place(d, v->device);
     if (e == hipSuccess && d->planes_on_device) {
-        rc = check_counts(d, v->copy, &total);
+        rc = check_counts(d, in_place, v->copy, &total);
         if (rc) {
             std::lock_guard<std::mutex> lock(v->mu);
             v->pending = false;
@@ -820,7 +855,7 @@ int vdi_replace_begin(vdi_t v, const vdi_desc *d, void *stream)
     }
     if (e == hipSuccess && !v->start) e = hipEventCreateWithFlags(&v->start, hipEventDisableTiming);
     if (e == hipSuccess && !v->ready) e = hipEventCreateWithFlags(&v->ready, hipEventDisableTiming);
-    if (e == hipSuccess && !v->stage && !d->planes_on_device) {
+    if (e == hipSuccess && !v->stage && !in_place) {
         v->stage_bytes = std::max<uint64_t>(256ull << 20, plane * 16);
         e = hipMallocAsync(&v->stage, v->stage_bytes, v->copy);
     }
@@ -828,7 +863,7 @@ int vdi_replace_begin(vdi_t v, const vdi_desc *d, void *stream)
     // upload waits for the work already enqueued on the caller's stream.
     if (e == hipSuccess) e = hipEventRecord(v->start, static_cast<hipStream_t>(stream));
     if (e == hipSuccess) e = hipStreamWaitEvent(v->copy, v->start, 0);
-    if (e == hipSuccess) e = upload_set(v->back, d, total, ob, gz, v->copy, v->stage, v->stage_bytes, &what);
+    if (e == hipSuccess) e = upload_set(v->back, d, in_place, total, ob, gz, v->copy, v->stage, v->stage_bytes, &what);
     if (e == hipSuccess) what = "replacement", e = hipEventRecord(v->ready, v->copy);
     std::lock_guard<std::mutex> lock(v->mu);
     if (e != hipSuccess) {

@@ -157,6 +157,15 @@ __host__ __device__ inline uint64_t plane_elems(int WO, int HO, int NS)
 // 64-bit offsets.
 __host__ __device__ inline bool fits32(int WO, int HO, int NS) { return plane_elems(WO, HO, NS) <= 0xffffffffull / 16; }
 
+// Whether a kernel on `device` may read a plane at p in place, in elements of
+// `align` bytes: memory of that device, aligned to them.  Memory of another
+// device is mapped only where peers were enabled, and host memory where it is
+// pinned; copies go anywhere.
+inline bool readable_in_place(const hipPointerAttribute_t &a, const void *p, int device, size_t align)
+{
+    return a.type == hipMemoryTypeDevice && !a.isManaged && a.device == device && reinterpret_cast<uintptr_t>(p) % align == 0;
+}
+
 // A resident VDI as the kernels see it.
 struct DevVDI {
     int32_t WO, HO, NS;

@@ -1,9 +1,13 @@
 """Calls at the edges of what the entry points accept (needs an MI355X): eyes
-far from the volume."""
+far from the volume; device planes that are not memory of the device or not
+aligned to a slot."""
+import ctypes
+
 import numpy as np
 import pytest
 
 import inputs
+from tests import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +49,45 @@ def test_far_eyes(eye, fov, u16):
             assert np.array_equal(a.cpu().numpy(), b)
     f64 = V.dvr(on_device(vol), bmin, bmax, cam, 25, 21, tf="knots4", precision="f64").cpu().numpy()
     assert np.array_equal(f64, ref.dvr.astype(np.float32))
+
+
+def created(V, d):
+    """A Vdi made from the descriptor d as it stands, by the C entry point alone."""
+    h = ctypes.c_void_p()
+    V._check(V.lib().vdi_create(ctypes.byref(d), ctypes.byref(h)))
+    v = V.Vdi.__new__(V.Vdi)
+    v._h = h
+    v.width, v.height, v.ns, v.store = d.width, d.height, d.max_supersegments, "f32"
+    return v
+
+
+def device_vdi(V, v):
+    return V.DeviceVDI(*(torch.from_numpy(a).cuda() for a in (v.count, v.depth, v.rgba)), v.camera, v.bmin, v.bmax,
+                       v.grid_k, v.grid_nz, v.grid_z)
+
+
+@pytest.mark.parametrize("how", ["pinned", "off by 4 bytes"])
+def test_planes_not_read_in_place(how):
+    """Copied to the device first: pinned host memory, and planes 4 bytes off their slots' alignment."""
+    V = _V()
+    v = synth.random_vdi(65, 33, 17, seed=82, alpha_max=0.3)
+    cam = inputs.orbit_camera(12.0)
+    dv = device_vdi(V, v)
+    if how == "pinned":
+        planes = [torch.from_numpy(a).pin_memory() for a in (v.count, v.depth, v.rgba)]
+        ptrs = [t.data_ptr() for t in planes]
+    else:
+        planes = [torch.cat((torch.zeros(4 // a.itemsize, dtype=torch.from_numpy(a).dtype), torch.from_numpy(a).reshape(-1))).cuda()
+                  for a in (v.count, v.depth, v.rgba)]
+        ptrs = [t.data_ptr() + 4 for t in planes]
+    torch.cuda.synchronize()
+    d, _keep = V._desc(dv, "f32", False, None, "f32")
+    d.count, d.depth, d.rgba = ptrs
+    with V.Vdi(v) as a, created(V, d) as b:
+        assert np.array_equal(b.grid(), a.grid()) and b.info().supersegments == int(v.count.sum())
+        want = a.render(cam, 60, 44)
+        assert torch.equal(b.render(cam, 60, 44), want)
+        V._check(V.lib().vdi_replace_begin(b.handle, ctypes.byref(d), None))
+        while not b.replace_poll():
+            pass
+        assert torch.equal(b.render(cam, 60, 44), want)
