@@ -132,7 +132,8 @@ typedef struct {
  * on return.  Synchronous for the calling thread: the upload runs on a stream
  * of its own, which is all it waits for, so work on the device's other
  * streams (a server's batches, renders of other VDIs) goes on meanwhile.
- * Device planes must be complete (their writers finished) when it is called.
+ * Device planes must be complete (their writers finished) when it is called, or
+ * written by work on the null stream, which is waited for.
  * Writes *out only on success.
  * Errors: VDI_ERR_ARG (null pointers, sizes, N_S or grid shape out of range,
  * non-finite camera or AABB, formats, and with validate != 0 an invalid list),

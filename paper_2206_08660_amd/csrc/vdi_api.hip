@@ -456,7 +456,10 @@ int check_counts(const vdi_desc *d, bool in_place, hipStream_t st, uint64_t *tot
         }
     } else {
         vdi::CountStats part[vdi::kCountBlocks], *d_part = nullptr;
-        hipError_t e = hipMallocAsync((void **)&d_part, sizeof part, st);
+        // `st` runs beside the null stream, on which the planes may have been
+        // written: a copy of them to the host would wait for it too.
+        hipError_t e = hipStreamSynchronize(nullptr);
+        if (e == hipSuccess) e = hipMallocAsync((void **)&d_part, sizeof part, st);
         if (e != hipSuccess) return hip_fail(e, "count statistics");
         e = vdi::launch_count_stats(d->count, plane, d_part, st);
         if (e == hipSuccess) e = hipMemcpyAsync(part, d_part, sizeof part, hipMemcpyDeviceToHost, st);

@@ -1,6 +1,6 @@
 """Calls at the edges of what the entry points accept (needs an MI355X): eyes
 far from the volume; device planes that are not memory of the device or not
-aligned to a slot."""
+aligned to a slot, or are still being written on the null stream."""
 import ctypes
 
 import numpy as np
@@ -91,3 +91,24 @@ def test_planes_not_read_in_place(how):
         while not b.replace_poll():
             pass
         assert torch.equal(b.render(cam, 60, 44), want)
+
+
+def test_planes_still_being_written_on_the_null_stream():
+    """vdi_create's own stream runs beside the null stream: it waits for it before it reads the planes."""
+    V = _V()
+    v = synth.random_vdi(200, 120, 20, seed=83, alpha_max=0.3)
+    full = device_vdi(V, v)
+    late = V.DeviceVDI(*(torch.zeros_like(t) for t in (full.count, full.depth, full.rgba)), v.camera, v.bmin, v.bmax,
+                       v.grid_k, v.grid_nz, v.grid_z)
+    d, _keep = V._desc(late, "f32", False, None, "f32")
+    busy = torch.rand((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    assert torch.cuda.current_stream().cuda_stream == 0
+    for _ in range(40):
+        torch.mm(busy, busy)
+    for a, b in zip((late.count, late.depth, late.rgba), (full.count, full.depth, full.rgba)):
+        a.copy_(b)
+    cam = inputs.orbit_camera(12.0)
+    with created(V, d) as b, V.Vdi(v) as a:
+        assert b.info().supersegments == int(v.count.sum())
+        assert torch.equal(b.render(cam, 60, 44), a.render(cam, 60, 44))
