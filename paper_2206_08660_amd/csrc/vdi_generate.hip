@@ -786,19 +786,27 @@ __device__ __forceinline__ void gather_f32(const GenVol &v, const double *u, Gat
         g.hi[m] = (typename Gather<K>::V)hi;
     });
 }
+// a (1 - w) + b w; as a + w (b - a), one instruction less, where voxels are
+// whole numbers: float voxels may be infinite, or far enough apart that b - a
+// is.
+template <VoxelKind K>
+__device__ __forceinline__ float lerp_f32(float a, float b, float w)
+{
+    return K == kU16 ? fmaf(w, b - a, a) : fmaf(b, w, a * (1.0f - w));
+}
 template <VoxelKind K>
 __device__ __forceinline__ float value_f32(const Gather<K> &g)
 {
     float c[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) c[m] = fmaf(g.w[0], (float)g.hi[m] - (float)g.lo[m], (float)g.lo[m]);
-    const float c0 = fmaf(g.w[1], c[1] - c[0], c[0]), c1 = fmaf(g.w[1], c[3] - c[2], c[2]);
-    const float r = fmaf(g.w[2], c1 - c0, c0);
+    for (int m = 0; m < 4; ++m) c[m] = lerp_f32<K>((float)g.lo[m], (float)g.hi[m], g.w[0]);
+    const float c0 = lerp_f32<K>(c[0], c[1], g.w[1]), c1 = lerp_f32<K>(c[2], c[3], g.w[1]);
+    const float r = lerp_f32<K>(c0, c1, g.w[2]);
     return K == kU16 ? r * (1.0f / 65535.0f) : r;
 }
 
 // Opacity of the transfer functions in FP32, and the colour it goes with (only
-// asked for where a sample is not transparent).
+// asked for where a sample is not transparent, or its colour not finite).
 __device__ __forceinline__ float tf_opacity_f32(int tf, float v)
 {
     if (tf == VDI_TF_RAMP) return 0.2f * fminf(fmaxf((v - 0.05f) * (1.0f / 0.95f), 0.0f), 1.0f);
@@ -872,6 +880,7 @@ constexpr int kDvrAhead = 4;
 template <VoxelKind K>
 __global__ __launch_bounds__(64) void k_dvr_f32(GenParams args, float4 *__restrict__ out)
 {
+#pragma clang fp contract(off)
     const GenParams &G = gen_args(args);
     int px, py;
     dvr_pixel(G.cam, px, py);
@@ -884,7 +893,9 @@ __global__ __launch_bounds__(64) void k_dvr_f32(GenParams args, float4 *__restri
         // Opacity 1 - (1 - a)^r as 1 - 2^(r log2(1 - a)) with the hardware
         // base-2 exponential and logarithm.
         const float r = (float)(len / G.ds);
-        // Voxel coordinate of sample q along each axis: u0 + q du (FP64).
+        // Voxel coordinate of sample q along each axis: u0 + q du (FP64, rounded
+        // as written: the only sample of a thin volume lies on its voxels'
+        // centres, where the last bit says which neighbour has weight 0).
         double u0[3], du[3];
         for (int a = 0; a < 3; ++a) {
             const double sc = G.vol.n(a) / (G.vol.bmax[a] - G.vol.bmin[a]);
@@ -898,13 +909,15 @@ __global__ __launch_bounds__(64) void k_dvr_f32(GenParams args, float4 *__restri
             for (int k = 0; k < kDvrAhead; ++k) {
                 // Past the last sample: the last one again, left out below.
                 const double qk = (double)min(q + k, N - 1);
-                const double u[3] = {fma(qk, du[0], u0[0]), fma(qk, du[1], u0[1]), fma(qk, du[2], u0[2])};
+                const double u[3] = {u0[0] + qk * du[0], u0[1] + qk * du[1], u0[2] + qk * du[2]};
                 gather_f32<K>(G.vol, u, g[k]);
             }
 #pragma unroll
             for (int k = 0; k < kDvrAhead; ++k) {
                 const float v = value_f32(g[k]), atf = tf_opacity_f32(G.tf, v);
-                if (atf > 0.0f && q + k < N && T > (float)kGenTTerm) {
+                // The ramp's colour is v itself: not a number after 0 times it.
+                const bool counts = atf > 0.0f || (K != kU16 && G.tf == VDI_TF_RAMP && !(fabsf(v) < INFINITY));
+                if (counts && q + k < N && T > (float)kGenTTerm) {
                     const float at = 1.0f - __builtin_amdgcn_exp2f(r * __builtin_amdgcn_logf(1.0f - atf)), w = T * at;
                     float c[3];
                     tf_colour_f32(G.tf, v, c);

@@ -112,3 +112,83 @@ def test_planes_still_being_written_on_the_null_stream():
     with created(V, d) as b, V.Vdi(v) as a:
         assert b.info().supersegments == int(v.count.sum())
         assert torch.equal(b.render(cam, 60, 44), a.render(cam, 60, 44))
+
+
+def dvr_f32_reference(vol, bmin, bmax, cam, W, H, tf):
+    """FP32 DVR in numpy: rays and sample positions in float64, interpolation lo (1 - w) + hi w, transfer function,
+    opacity and compositing in float32."""
+    f4 = np.float32
+    e, t, u = (np.array(x, dtype=np.float64) for x in (cam.eye, cam.target, cam.up))
+    F = (t - e) / np.linalg.norm(t - e)
+    R = np.cross(F, u)
+    R /= np.linalg.norm(R)
+    U = np.cross(R, F)
+    th = np.tan(float(f4(cam.fov_y_deg)) * np.pi / 360)
+    xc, yc = -1 + (2 * np.arange(W) + 1) / W, -1 + (2 * np.arange(H) + 1) / H
+    d = F + xc[None, :, None] * th * W / H * R + yc[:, None, None] * th * U
+    d /= np.linalg.norm(d, axis=2, keepdims=True)
+    lo, hi = float(f4(cam.near)) / (d @ F), np.full((H, W), np.inf)
+    for a in range(3):
+        ta, tb = (bmin[a] - e[a]) / d[..., a], (bmax[a] - e[a]) / d[..., a]
+        lo, hi = np.maximum(lo, np.minimum(ta, tb)), np.minimum(hi, np.maximum(ta, tb))
+    hit = hi > lo
+    n = np.array(vol.shape[::-1])
+    ds = max(b - a for a, b in zip(bmin, bmax)) / n.max()
+    N = np.where(hit, np.maximum(np.ceil((hi - lo) / ds - 1e-9), 1), 0)
+    with np.errstate(all="ignore"):
+        ln = np.where(hit, (hi - lo) / N, 0)
+        r = (ln / ds).astype(f4)
+        acc, T = np.zeros((H, W, 3), f4), np.ones((H, W), f4)
+        sc = n / (np.array(bmax) - np.array(bmin))
+        u0 = (e + (np.where(hit, lo, 0) + 0.5 * ln)[..., None] * d - np.array(bmin)) * sc - 0.5
+        du = ln[..., None] * d * sc
+        for q in range(int(N.max())):
+            live = (q < N) & (T > f4(1e-5))
+            uv = u0 + q * du
+            i0 = np.floor(uv).astype(int)
+            w = (uv - i0).astype(f4)
+            a, b = np.clip(i0, 0, n - 1), np.clip(i0 + 1, 0, n - 1)
+            at = lambda x, y, z: vol[z[..., 2], y[..., 1], x[..., 0]]
+            mix = lambda p, q_, k: p * (1 - w[..., k]) + q_ * w[..., k]
+            c = [mix(at(a, y, z), at(b, y, z), 0) for z in (a, b) for y in (a, b)]
+            v = mix(mix(c[0], c[1], 1), mix(c[2], c[3], 1), 2)
+            if tf == "ramp":
+                col = np.stack((v, f4(0.25) + f4(0.5) * v, 1 - v), -1)
+                op = f4(0.2) * np.fmin(np.fmax((v - f4(0.05)) / f4(0.95), f4(0)), f4(1))
+            else:
+                v = np.fmin(np.fmax(v, f4(0)), f4(1))
+                kv, ka = np.array([0, 0.25, 0.55, 1], f4), np.array([0, 0, 0.04, 0.12], f4)
+                kc = np.array([[0.1, 0.2, 0.8], [0.1, 0.7, 0.9], [0.95, 0.9, 0.3], [0.9, 0.15, 0.1]], f4)
+                s = (v >= kv[1]).astype(int) + (v >= kv[2])
+                x = (v - kv[s]) / (kv[s + 1] - kv[s])
+                col, op = kc[s] + x[..., None] * (kc[s + 1] - kc[s]), ka[s] + x * (ka[s + 1] - ka[s])
+            al = np.where(op > 0, 1 - np.power(1 - op, r), f4(0)).astype(f4)
+            acc = np.where(live[..., None], acc + (T * al)[..., None] * col, acc)
+            T = np.where(live, T * (1 - al), T)
+    return np.concatenate((acc, (1 - T)[..., None]), 2)
+
+
+# Infinite and NaN voxels, and neighbours whose difference overflows FP32.
+@pytest.mark.parametrize("tf,values", [("knots4", (np.inf, -np.inf)), ("knots4", (np.inf,)), ("knots4", (np.nan,)),
+                                       ("knots4", (3e38, -3e38)), ("ramp", (np.inf,)), ("ramp", (-np.inf,)),
+                                       ("ramp", (np.nan,))])
+@pytest.mark.parametrize("dims", [(12, 11, 10), (1, 11, 10)])
+def test_dvr_of_volumes_with_values_out_of_range(dims, tf, values):
+    V = _V()
+    nx, ny, nz = dims
+    rng = np.random.default_rng(17)
+    vol = (0.5 + 0.3 * rng.random((nz, ny, nx))).astype(np.float32)
+    for k in range(6):
+        vol[tuple(rng.integers(0, n) for n in vol.shape)] = values[k % len(values)]
+    bmin, bmax = inputs.aabb_for(dims)
+    cam = inputs.orbit_camera(23.0, radius=1.6)
+    generated = inputs.generate_vdi(vol, cam, 61, 47, 6, inputs.TF_RAMP if tf == "ramp" else inputs.TF_KNOTS4, 0.01)
+    for precision, ref in (("f64", generated.dvr.astype(np.float32)),
+                           ("f32", dvr_f32_reference(vol, bmin, bmax, cam, 61, 47, tf))):
+        got = V.dvr(on_device(vol), bmin, bmax, cam, 61, 47, tf=tf, precision=precision).cpu().numpy()
+        same = {k: bool(np.array_equal(f(got), f(ref))) for k, f in (("nan", np.isnan), ("inf", np.isposinf), ("-inf", np.isneginf))}
+        fin = np.isfinite(ref) & np.isfinite(got)
+        off = float(np.abs(got[fin] - ref[fin]).max())
+        print(f"[gpu] {precision} {tf} {values} {dims}: {same}, {int((~np.isfinite(ref)).sum())} not finite, off {off:.1e}",
+              flush=True)
+        assert fin.any() and all(same.values()) and off <= 1e-4, precision
