@@ -373,17 +373,20 @@ constexpr int kWin = VDI_WIN;
 // and (double)x < z exactly when x < above(z), where below(z) is the largest
 // float <= z and above(z) the smallest float >= z.  The searches compare
 // float depths against these bounds, with the same outcome as comparing in
-// double precision.  For z > 0, as depths along a ray are (it is clipped to
-// V_O's near plane): the neighbouring float is then one bit pattern away.
+// double precision.  The neighbouring float is one bit pattern away, up or down
+// by the sign (a depth along a ray is positive but for rounding at a near plane
+// that is tiny beside the eye's distance).
 VDI_HD inline float float_below(double z)
 {
     const float f = (float)z;
-    return __builtin_bit_cast(float, __builtin_bit_cast(int32_t, f) - ((double)f > z ? 1 : 0));
+    const int32_t i = __builtin_bit_cast(int32_t, f);
+    return __builtin_bit_cast(float, (double)f > z ? i - (i >> 31 | 1) : i);
 }
 VDI_HD inline float float_above(double z)
 {
     const float f = (float)z;
-    return __builtin_bit_cast(float, __builtin_bit_cast(int32_t, f) + ((double)f < z ? 1 : 0));
+    const int32_t i = __builtin_bit_cast(int32_t, f);
+    return __builtin_bit_cast(float, (double)f < z ? i + (i >> 31 | 1) : i);
 }
 
 // A ray moving to larger depth usually finds its answer at or after the
