@@ -158,11 +158,13 @@ struct Ray {
 };
 
 // Keep t with a + b t >= 0.  A slope under 1e-300 is a zero: its crossing lies
-// beyond every ray, and its reciprocal beyond the double range.
+// beyond every ray, and its reciprocal beyond the double range.  A crossing
+// beyond the double range is infinite, and has no remainder to correct it by.
 VDI_HD inline bool clip(double a, double b, double &lo, double &hi)
 {
     if (fabs(b) < 1e-300) return a >= 0.0;
-    const double rb = rcp64(b), q = -a * rb, t = fma(fma(-b, q, -a), rb, q);  // -a / b
+    const double rb = rcp64(b), q = -a * rb;
+    const double t = fabs(q) < __builtin_huge_val() ? fma(fma(-b, q, -a), rb, q) : q;  // -a / b
     if (b > 0.0)
         lo = fmax(lo, t);
     else

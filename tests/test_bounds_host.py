@@ -1,6 +1,7 @@
 """The ray walkers' arithmetic of bounds on the host (hipcc; nothing runs on a
 GPU): the largest float at or below a depth and the smallest at or above it, for
-depths of either sign."""
+depths of either sign, and the clipping of a ray's parameter range against
+IEEE division, up to quotients beyond the double range."""
 import ctypes
 import os
 import shutil
@@ -44,3 +45,23 @@ def test_floats_next_to_a_depth(host):
         down = np.where(near.astype(np.float64) > z, np.nextafter(near, np.float32(-np.inf)), near)
         up = np.where(near.astype(np.float64) < z, np.nextafter(near, np.float32(np.inf)), near)
     assert np.array_equal(below, down) and np.array_equal(above, up)
+
+
+def test_clip_is_a_division(host):
+    rng = np.random.default_rng(4)
+    a = np.concatenate(([0.0], 10.0 ** rng.uniform(-30, 38, 200)))
+    b = np.concatenate(([0.0], 10.0 ** rng.uniform(-299.9, 3, 200), 10.0 ** rng.uniform(-5, 1, 100)))
+    a, b = (x.ravel() for x in np.meshgrid(np.concatenate((a, -a)), np.concatenate((b, -b))))
+    lo, hi = np.zeros(len(a)), np.full(len(a), np.inf)
+    ok = np.zeros(len(a), np.int32)
+    host.host_clip(p(a), p(b), len(a), p(lo), p(hi), p(ok))
+    with np.errstate(all="ignore"):
+        t = -a / b
+    want_lo, want_hi = np.where(b > 0, np.maximum(0.0, t), 0.0), np.where(b < 0, np.minimum(np.inf, t), np.inf)
+    empty = np.where(b == 0, a < 0, ~(want_hi > want_lo))
+    assert np.isinf(t[b != 0]).sum() > 100
+    assert np.array_equal((ok == 0) | ~(hi > lo), empty)
+    live = ~empty
+    with np.errstate(invalid="ignore"):
+        for got, want in ((lo[live], want_lo[live]), (hi[live], want_hi[live])):
+            assert ((got == want) | (np.abs(got - want) <= 4e-16 * np.abs(want))).all()
