@@ -175,8 +175,8 @@ int vdi_render(vdi_t v, const vdi_camera *cam_VN, int32_t width, int32_t height,
  * one colour format form one launch, exact before preview frames and those
  * whose rays cross most lists first, and the upsampling of all downsampled
  * frames another, so the long rays of one frame run beside the tiles of the
- * others.  Frames may
- * name different VDIs, all resident on the device of hip_stream.
+ * others (small exact frames, if there are many, form one of their own).
+ * Frames may name different VDIs, all resident on the device of hip_stream.
  *   n              1 .. VDI_BATCH_MAX_FRAMES.
  *   vdis, cams, widths, heights, D_I, D_R, outs
  *                  host arrays of n entries; outs[i] are DEVICE pointers
@@ -463,8 +463,8 @@ int vdi_image_quality(const float *image, const float *reference, int32_t width,
  * submitting thread within vdi_server_submit if a stream is free then,
  * otherwise by a scheduler thread owned by the server.  One kernel launch
  * per colour format covers the tiles of all its requests, whatever their mode,
- * resolution, viewpoint and preview level, and one more upsamples those with
- * D_I > 1.
+ * resolution, viewpoint and preview level (one more those of small exact
+ * requests, if there are many), and one more upsamples those with D_I > 1.
  * With two or more streams the next batches start while earlier ones
  * drain.  A request is done when its batch is.  A request's image is
  * identical to vdi_render's with the same arguments.

@@ -172,7 +172,7 @@ int build_frame(const vdi::VdiSet &S, const vdi_camera &cam, int w, int h, doubl
     f.search = VDI_SEARCH_WINDOW;
     f.parts = vdi::preview_parts(w, h);
     f.lists = lists_crossed(S.dev, f);
-    f.xparts = vdi::exact_parts(w, h, f.lists);
+    f.xparts = f.xlanes = vdi::exact_parts(w, h, f.lists);
     return VDI_OK;
 }
 

@@ -36,16 +36,18 @@ constexpr int kXTileW = VDI_EXACT_TW;
 constexpr int kXTileH = 64 / VDI_EXACT_TW;
 constexpr int kXcds = 8;
 
-// Exact rays of small frames are split over `parts` adjacent lanes, by cutting
-// their parameter range: such a frame lasts as long as its longest ray, whose
-// lists follow one another.  A power of two up to 16 that keeps the launch
+// Exact rays of small frames are cut into `parts` parts, each for an adjacent
+// lane (but see split_launch): such a frame lasts as long as its longest ray,
+// whose lists follow one another.  A power of two up to 16 that keeps the launch
 // within 2^18 lanes (2^19 where rays cross 128 lists or more), and a part at
 // one list or more: `lists` is the most that the frame's rays cross, as its
 // set-up estimates.  Where the line lies (us, whole rays -> split; 1280 x 720 /
 // N_S 20 VDI at 30 deg, 128 x 128 / N_S 16 VDI at 5 deg): 128 x 128 frame 941
 // -> 114, 50 -> 26; 256 x 256 941 -> 260, 50 -> 36; 512 x 512 965 -> 703; but
 // 1280 x 720 1053 -> 1017 alone and 6560 -> 7560 in a server's mix, since
-// split rays cost set-up and shared lines that a full device pays for.
+// split rays cost set-up and shared lines that a full device pays for.  The
+// number of parts is the frame's own, whatever it is rendered with: a frame of a
+// batch is the single render's, bit for bit.
 #ifndef VDI_EXACT_LANES
 #define VDI_EXACT_LANES 262144
 #endif
@@ -56,6 +58,20 @@ inline int exact_parts(int w, int h, double lists)
     while (p < 16 && (double)w * h * p * 2 <= lanes && lists >= p * 2.0) p <<= 1;
     return p;
 }
+// Whether the frames of a launch (or in flight on a persistent one) whose rays
+// are in parts, `rays` rays in all, take a lane for each part, or one lane that
+// folds the parts of a ray one after another.  Split, n frames cost n times a
+// frame once they fill the device; folded, they last as long as the longest ray
+// until they do.  Where the line lies (us, split / folded; frames of the 1280 x
+// 720 / N_S 20 VDI at 30 deg, and at 5 deg): 16 of 128 x 128 1058 / 1478, 429 /
+// 411; 24 1560 / 1668, 633 / 486; 32 2074 / 1861, 852 / 621; 64 4164 / 3323,
+// 1754 / 1109; of 256 x 256 4 865 / 1366, 234 / 273; 6 1254 / 1563, 327 / 315; 8
+// 1644 / 1659, 422 / 363; 16 3218 / 3047, 809 / 661.  Rays in one part would
+// take 3156 and 719 for the 64: a cut costs about as much as a list.
+#ifndef VDI_SPLIT_RAYS
+#define VDI_SPLIT_RAYS 393216
+#endif
+inline bool split_launch(double rays) { return rays <= VDI_SPLIT_RAYS; }
 // An exact wavefront renders 64 / parts rays, at most kXTileH rows tall; the
 // `parts` lanes of a ray are adjacent.
 __host__ __device__ inline void exact_tile_dims(int parts, int &tw, int &th)
@@ -202,7 +218,8 @@ struct Frame {
     int32_t ess, search;
     double DR;                 // > 0: along-ray subsampling
     int32_t parts;             // preview: lanes per ray (preview_parts)
-    int32_t xparts;            // exact: lanes per ray (exact_parts)
+    int32_t xparts;            // exact: parts of a ray (exact_parts)
+    int32_t xlanes;            // exact: lanes per ray, xparts or 1 (split_launch)
     double lists;              // about the most lists that a ray crosses
     float4 *out;               // [H][W]
     // counters (instrumented kernels only)
@@ -381,8 +398,11 @@ hipError_t launch_set_gz(const float *z, int32_t n, float *gz, hipStream_t strea
 // job's VDI does not fit 32-bit offsets (fits32).
 // Kinds of jobs, each with a kernel of its own, and the kernel that renders
 // all of them in one launch.
-enum JobKind { kExactJob, kSplitJob, kPreviewJob, kJobKinds, kMixedJobs = kJobKinds };
-inline JobKind job_kind(bool preview, const Frame &f) { return preview ? kPreviewJob : (f.xparts > 1 ? kSplitJob : kExactJob); }
+enum JobKind { kExactJob, kFoldJob, kSplitJob, kPreviewJob, kJobKinds, kMixedJobs = kJobKinds };
+inline JobKind job_kind(bool preview, const Frame &f)
+{
+    return preview ? kPreviewJob : (f.xlanes > 1 ? kSplitJob : (f.xparts > 1 ? kFoldJob : kExactJob));
+}
 hipError_t launch_batch_render(const BatchJob *jobs, int32_t njobs, uint32_t nblocks, int32_t fmt, JobKind kind,
                                bool wide, hipStream_t stream);
 hipError_t launch_batch_upsample(const UpsampleJob *jobs, int32_t njobs, uint32_t nblocks, hipStream_t stream);

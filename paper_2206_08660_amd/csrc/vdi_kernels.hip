@@ -47,6 +47,13 @@ namespace {
 #define VDI_BATCH_WAVES 7
 #endif
 #define VDI_BATCH_OCC __attribute__((amdgpu_waves_per_eu(VDI_BATCH_WAVES)))
+// Folded exact tiles: the fewest wavefronts without spills (6 with 19 VGPRs
+// spilled: 64 frames of 256 x 256 11.55 against 11.60 ms, of 128 x 128 3.44
+// against 3.38).
+#ifndef VDI_FOLD_WAVES
+#define VDI_FOLD_WAVES 5
+#endif
+#define VDI_FOLD_OCC __attribute__((amdgpu_waves_per_eu(VDI_FOLD_WAVES)))
 
 // Store of an output pixel: plain, or (WT) written through to device memory
 // as two relaxed system-scope atomic stores of 8 bytes, for the persistent
@@ -99,8 +106,8 @@ VDI_HDI bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &
     return false;
 }
 
-// One exact tile of kXTileW x kXTileH rays.
-template <int FMT, int SEARCH, bool ESS, typename Idx, bool WT = false>
+// One exact tile of kXTileW x kXTileH rays.  FOLD: rays that may be in parts.
+template <int FMT, int SEARCH, bool ESS, typename Idx, bool WT = false, bool FOLD = false>
 __device__ __forceinline__ void exact_tile(const DevVDI &V, const Frame &F, const float *s_gz, int tile_index)
 {
     int x0, y0;
@@ -110,7 +117,9 @@ __device__ __forceinline__ void exact_tile(const DevVDI &V, const Frame &F, cons
     float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (meets) {
         Counters cnt = {0, 0};
-        o = trace_exact<FMT, SEARCH, ESS, false, Idx>(V, F, s_gz, px, py, cnt);
+        Accum a = {0.0f, 0.0f, 0.0f, 1.0f};
+        trace_exact_part<FMT, SEARCH, ESS, false, Idx, FOLD>(V, F, s_gz, px, py, 0, FOLD ? F.xparts : 1, a, cnt);
+        o = to_rgba(a);
     }
     store_px<WT>(&F.out[(uint64_t)py * F.W + px], o);
 }
@@ -136,7 +145,7 @@ __device__ __forceinline__ const RenderArgs &render_args(const RenderArgs &param
 #endif
 }
 
-// One exact tile whose rays are split over F.xparts adjacent lanes
+// One exact tile whose rays are split over F.xlanes adjacent lanes
 // (exact_tile_dims).  The parts are walked from full transmittance and
 // combined in ray order.  Where a ray terminates inside a part, that part is
 // walked again on top of the parts before it, so that it stops where the whole
@@ -144,7 +153,7 @@ __device__ __forceinline__ const RenderArgs &render_args(const RenderArgs &param
 template <int FMT, int SEARCH, bool ESS, typename Idx, bool WT = false>
 __device__ __forceinline__ void split_tile(const DevVDI &V, const Frame &F, const float *s_gz, int tile_index)
 {
-    const int parts = F.xparts;
+    const int parts = F.xlanes;
     int tw, th, x0, y0;
     exact_tile_dims(parts, tw, th);
     const bool meets = place_tile(F, tw, th, VDI_BAND_ROWS / th, tile_index, x0, y0, true);
@@ -293,12 +302,12 @@ __device__ __forceinline__ void batch_tile(const BatchJob *__restrict__ jobs, in
     if (local >= J.ntiles) return;  // padding block: the whole workgroup leaves
     for (int i = threadIdx.x; i <= J.V.gnz; i += kBlock) s_gz[i] = J.V.gz[i];
     __syncthreads();
-    if (KIND == kSplitJob || (KIND == kMixedJobs && J.F.DR == 0.0 && J.F.xparts > 1)) {
+    if (KIND == kSplitJob || (KIND == kMixedJobs && J.F.DR == 0.0 && J.F.xlanes > 1)) {
         split_tile<FMT, VDI_SEARCH_WINDOW, true, Idx>(J.V, J.F, s_gz, (int)local);
     } else if (KIND == kPreviewJob || (KIND == kMixedJobs && J.F.DR > 0.0)) {
         preview_tile<FMT, Idx>(J.V, J.F, s_gz, (int)local);
     } else {
-        exact_tile<FMT, VDI_SEARCH_WINDOW, true, Idx>(J.V, J.F, s_gz, (int)local);
+        exact_tile<FMT, VDI_SEARCH_WINDOW, true, Idx, false, KIND == kFoldJob>(J.V, J.F, s_gz, (int)local);
     }
 }
 
@@ -310,11 +319,17 @@ __global__ __launch_bounds__(kBlock) VDI_BATCH_OCC void k_render_batch(const Bat
     batch_tile<FMT, kExactJob, Idx>(jobs, njobs);
 }
 template <int FMT, typename Idx>
+__global__ __launch_bounds__(kBlock) VDI_FOLD_OCC void k_render_batch_fold(const BatchJob *__restrict__ jobs, int njobs)
+{
+    batch_tile<FMT, kFoldJob, Idx>(jobs, njobs);
+}
+template <int FMT, typename Idx>
 __global__ __launch_bounds__(kBlock) VDI_SPLIT_OCC void k_render_batch_split(const BatchJob *__restrict__ jobs, int njobs)
 {
     batch_tile<FMT, kSplitJob, Idx>(jobs, njobs);
 }
-// Jobs of several kinds in one launch: launches on a stream follow one
+// Jobs of several kinds (but folded ones, whose walker would add as many spills
+// again) in one launch: launches on a stream follow one
 // another, and each ended on a nearly empty device.  Exact tiles come first, the
 // shorter preview tiles fill their end.  Although its 80 registers spill
 // 20-28 (5 wavefronts without spills: 2966 us), a launch for all beats one for
@@ -503,10 +518,10 @@ __global__ __launch_bounds__(kBlock) VDI_PERSIST_OCC void k_persist(const PHost 
             if (J.preview) {
                 preview_tile<FMT, uint64_t, false, true>(J.R.V, J.R.F, s_gz, (int)local);
             } else {
-                if (J.R.F.xparts > 1)
+                if (J.R.F.xlanes > 1)
                     split_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
                 else
-                    exact_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
+                    exact_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true, true>(J.R.V, J.R.F, s_gz, (int)local);
             }
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores have completed
             __syncthreads();                // and s_gz is free for the next tile
@@ -747,7 +762,7 @@ hipError_t launch_exact_fmt(const DevVDI &v, const Frame &f, dim3 grid, hipStrea
         if (!ess) k = k_render_exact<FMT, VDI_SEARCH_SEEDED, false, COUNT, Idx>;
     }
     if constexpr (!COUNT)
-        if (f.xparts > 1) {
+        if (f.xlanes > 1) {
             k = k_render_split<FMT, VDI_SEARCH_SEEDED, true, Idx>;
             switch (f.search) {
             case VDI_SEARCH_BINARY:
@@ -776,7 +791,7 @@ hipError_t launch_exact_of(const DevVDI &v, const Frame &f, bool counters, dim3 
     if (f.search != VDI_SEARCH_WINDOW || !fits32(v.WO, v.HO, v.NS)) return launch_exact_fmt<FMT, false, uint64_t>(v, f, grid, s);
     auto k = f.ess ? k_render_exact<FMT, VDI_SEARCH_WINDOW, true, false, uint32_t>
                    : k_render_exact<FMT, VDI_SEARCH_WINDOW, false, false, uint32_t>;
-    if (f.xparts > 1)
+    if (f.xlanes > 1)
         k = f.ess ? k_render_split<FMT, VDI_SEARCH_WINDOW, true, uint32_t> : k_render_split<FMT, VDI_SEARCH_WINDOW, false, uint32_t>;
     k<<<grid, kBlock, 0, s>>>(RenderArgs{v, f});
     return hipGetLastError();
@@ -787,7 +802,7 @@ hipError_t launch_exact_of(const DevVDI &v, const Frame &f, bool counters, dim3 
 
 hipError_t launch_render_exact(const DevVDI &v, const Frame &f, bool counters, hipStream_t s)
 {
-    const dim3 g(exact_tiles(f.W, f.H, counters ? 1 : f.xparts));
+    const dim3 g(exact_tiles(f.W, f.H, counters ? 1 : f.xlanes));
     switch (v.fmt) {
     case VDI_F16: return launch_exact_of<VDI_F16>(v, f, counters, g, s);
     case VDI_BF16: return launch_exact_of<VDI_BF16>(v, f, counters, g, s);
@@ -826,6 +841,7 @@ template <int FMT>
 hipError_t launch_batch_of(const BatchJob *jobs, int32_t njobs, dim3 grid, JobKind kind, bool wide, hipStream_t s)
 {
     auto k = wide ? k_render_batch<FMT, uint64_t> : k_render_batch<FMT, uint32_t>;
+    if (kind == kFoldJob) k = wide ? k_render_batch_fold<FMT, uint64_t> : k_render_batch_fold<FMT, uint32_t>;
     if (kind == kSplitJob) k = wide ? k_render_batch_split<FMT, uint64_t> : k_render_batch_split<FMT, uint32_t>;
     if (kind == kMixedJobs) k = wide ? k_render_batch_mixed<FMT, uint64_t> : k_render_batch_mixed<FMT, uint32_t>;
     if (kind == kPreviewJob) k = wide ? k_render_batch_preview<FMT, uint64_t> : k_render_batch_preview<FMT, uint32_t>;

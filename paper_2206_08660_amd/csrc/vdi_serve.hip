@@ -55,6 +55,14 @@ constexpr int kMaxBatch = 256;                 // requests per batch
 #define VDI_BATCH_TILES ((1ull << 23) / (kTileW * kTileH))
 #endif
 constexpr uint64_t kBatchTiles = VDI_BATCH_TILES;
+// Rays in parts of a frame (split_launch).
+double part_rays(bool preview, const Frame &f) { return !preview && f.xparts > 1 ? (double)f.W * f.H : 0.0; }
+// Settle how an exact job's rays in parts are walked in its launch.
+void place_parts(BatchJob &job, bool split)
+{
+    job.F.xlanes = split ? job.F.xparts : 1;
+    job.ntiles = exact_tiles(job.F.W, job.F.H, job.F.xlanes);
+}
 // Upsampling tiles per batch: keeps every launch far below 2^32 work-items.
 constexpr uint64_t kBatchUpTiles = 1ull << 22;
 
@@ -122,6 +130,7 @@ struct Persist {
     uint64_t tiles = 0;                                // global tiles given out by it
     uint64_t mem_epoch = 0;                            // g_mem_epoch at its start
     std::vector<uint64_t> published;                   // its tickets not yet retired
+    double rays = 0.0;                                 // ... and their rays in parts (part_rays)
     std::chrono::steady_clock::time_point idle_since;
 };
 
@@ -182,34 +191,38 @@ void launch_batch(vdi_server_s *s, Lane &L)
         take.push_back(s->queue.front());
         s->queue.pop_front();
     }
-    // Job tables: one group per format, exact frames before previews, each
-    // sorted by tile0.
+    double rays = 0.0;
+    for (uint64_t tk : take) rays += part_rays(s->requests.at(tk).preview, s->requests.at(tk).job.F);
+    for (uint64_t tk : take)
+        if (!s->requests.at(tk).preview) place_parts(s->requests.at(tk).job, split_launch(rays));
+    // Job tables: one group per format, exact frames before previews, and one
+    // for its folded frames, each sorted by tile0.
     int nj = 0, nu = 0;
-    int group_start[3], group_count[3];
-    uint32_t group_blocks[3];
-    JobKind group_kind[3];
+    int group_start[6], group_count[6];
+    uint32_t group_blocks[6];
+    JobKind group_kind[6];
     bool wide = false;
     // Frames whose rays cross most lists first: a launch ends on its last ones.
     std::vector<uint64_t> order(take);
     std::stable_sort(order.begin(), order.end(), [&](uint64_t a, uint64_t b) {
         return s->requests.at(a).job.F.lists > s->requests.at(b).job.F.lists;
     });
-    for (int f = 0; f < 3; ++f) {
-        group_start[f] = nj;
+    for (int g = 0; g < 6; ++g) {
+        group_start[g] = nj;
         uint64_t t = 0;
         for (int p = 0; p < kJobKinds; ++p)
             for (uint64_t tk : order) {
                 Request &r = s->requests.at(tk);
-                if (job_kind(r.preview, r.job.F) != p || r.fmt != f) continue;
-                group_kind[f] = nj == group_start[f] || group_kind[f] == p ? (JobKind)p : kMixedJobs;
+                if (job_kind(r.preview, r.job.F) != p || (p == kFoldJob) != (g >= 3) || r.fmt != g % 3) continue;
+                group_kind[g] = nj == group_start[g] || group_kind[g] == p ? (JobKind)p : kMixedJobs;
                 t = align_up(t);
                 r.job.tile0 = (uint32_t)t;
                 t += r.job.ntiles;
                 wide = wide || !fits32(r.job.V.WO, r.job.V.HO, r.job.V.NS);
                 L.h_jobs[nj++] = r.job;
             }
-        group_count[f] = nj - group_start[f];
-        group_blocks[f] = (uint32_t)t;
+        group_count[g] = nj - group_start[g];
+        group_blocks[g] = (uint32_t)t;
     }
     uint64_t tu = 0;
     for (uint64_t tk : take) {
@@ -223,9 +236,10 @@ void launch_batch(vdi_server_s *s, Lane &L)
     hipError_t e = hipMemcpyAsync(L.d_jobs, L.h_jobs, sizeof(BatchJob) * nj, hipMemcpyHostToDevice, L.stream);
     if (e == hipSuccess && nu)
         e = hipMemcpyAsync(L.d_up, L.h_up, sizeof(UpsampleJob) * nu, hipMemcpyHostToDevice, L.stream);
-    for (int f = 0; f < 3 && e == hipSuccess; ++f)
-        if (group_count[f])
-            e = launch_batch_render(L.d_jobs + group_start[f], group_count[f], group_blocks[f], f, group_kind[f], wide, L.stream);
+    for (int g = 0; g < 6 && e == hipSuccess; ++g)
+        if (group_count[g])
+            e = launch_batch_render(L.d_jobs + group_start[g], group_count[g], group_blocks[g], g % 3, group_kind[g], wide,
+                                    L.stream);
     if (e == hipSuccess && nu) e = launch_batch_upsample(L.d_up, nu, (uint32_t)tu, L.stream);
     if (e == hipSuccess) e = hipEventRecord(L.done, L.stream);
     L.tickets = std::move(take);
@@ -310,6 +324,8 @@ void persist_pump(vdi_server_s *s)
         Request &r = s->requests.at(tk);
         if (!P.running) persist_launch(s, r.fmt);
         if (s->err) return;
+        const double rays = part_rays(r.preview, r.job.F);
+        if (!r.preview) place_parts(r.job, split_launch(P.rays + rays));
         const uint64_t t0 = align_up(P.tiles);
         const uint64_t u0 = align_up(t0 + r.job.ntiles);
         const uint64_t end = r.down ? u0 + r.up.ntiles : t0 + r.job.ntiles;
@@ -341,6 +357,7 @@ void persist_pump(vdi_server_s *s)
         __atomic_store_n(&P.h_ctl->tail.v, (unsigned long long)(j + 1), __ATOMIC_RELEASE);
         s->queue.pop_front();
         P.published.push_back(tk);
+        P.rays += rays;
         s->st.queued = (int32_t)s->queue.size();
     }
 }
@@ -353,6 +370,7 @@ bool persist_retire(vdi_server_s *s)
     for (size_t i = 0; i < P.published.size();) {
         const uint64_t tk = P.published[i];
         if (__atomic_load_n(&P.h_done[s->requests.at(tk).slot], __ATOMIC_ACQUIRE) != 0u) {
+            P.rays -= part_rays(s->requests.at(tk).preview, s->requests.at(tk).job.F);
             finish_request(s, tk);
             P.published[i] = P.published.back();
             P.published.pop_back();
@@ -597,7 +615,8 @@ int submit(vdi_server_t s, vdi_t v, const vdi_camera *cam, int32_t W, int32_t H,
     r.job.F.ess = 1;
     r.job.F.search = VDI_SEARCH_WINDOW;
     r.job.tile0 = 0;
-    r.job.ntiles = D_R > 0.0f ? vdi::preview_tiles(w, h) : vdi::exact_tiles(w, h, r.job.F.xparts);
+    // An exact request's tiles are counted in whole rays until its launch says otherwise.
+    r.job.ntiles = D_R > 0.0f ? vdi::preview_tiles(w, h) : vdi::exact_tiles(w, h, 1);
     r.fmt = S.dev.fmt;
     r.preview = D_R > 0.0f;
     r.down = down;
@@ -713,6 +732,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
     if (!vdis || !cams || !widths || !heights || !D_I || !D_R || !outs) return set_error(VDI_ERR_ARG, "null array");
     std::vector<BatchItem> items((size_t)n);
     bool wide = false;
+    double rays = 0.0;
     int device = -1;
     for (int i = 0; i < n; ++i) {
         int rc = check_render_args(vdis[i], &cams[i], widths[i], heights[i], D_I[i], D_R[i], outs[i]);
@@ -735,7 +755,8 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         it.fmt = S.dev.fmt;
         it.preview = D_R[i] > 0.0f;
         it.down = (w != widths[i] || h != heights[i]);
-        it.job.ntiles = it.preview ? preview_tiles(w, h) : exact_tiles(w, h, it.job.F.xparts);
+        rays += part_rays(it.preview, it.job.F);
+        if (it.preview) it.job.ntiles = preview_tiles(w, h);
         if (it.down) {
             // Rounded up to a power of two (at least 1 MiB), as for vdi_render.
             it.lo_bytes = (size_t)1 << 20;
@@ -746,6 +767,8 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
             it.job.F.out = reinterpret_cast<float4 *>(outs[i]);
         }
     }
+    for (BatchItem &it : items)
+        if (!it.preview) place_parts(it.job, split_launch(rays));
     hipError_t e = hipSetDevice(device);
     if (e != hipSuccess) return hip_error(e, "hipSetDevice");
     hipMemPool_t pool = nullptr;
@@ -791,7 +814,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         release();
         return hip_error(e, "pinned job tables");
     }
-    // Job tables: one group per format, exact frames before previews, cut into launches of at most
+    // Job tables: one group per format, exact frames before previews, and one for its folded frames, cut into launches of at most
     // kLaunchBlocks blocks; a job starts at a multiple of the XCD count.
     std::vector<Launch> launches, up_launches;
     {
@@ -800,14 +823,15 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         R->next = (k + 1) % kRingSlots;
         e = hipEventSynchronize(R->copied[k]);
         int nj = 0, nu = 0;
-        for (int f = 0; f < 3 && e == hipSuccess; ++f) {
+        for (int g = 0; g < 6 && e == hipSuccess; ++g) {
+            const int f = g % 3;
             uint64_t t = 0;
             int start = nj;
             JobKind kind = kExactJob;
             for (int p = 0; p < kJobKinds; ++p)
                 for (const BatchItem *item : order) {
                     const BatchItem &it = *item;
-                    if (job_kind(it.preview, it.job.F) != p || it.fmt != f) continue;
+                    if (job_kind(it.preview, it.job.F) != p || (p == kFoldJob) != (g >= 3) || it.fmt != f) continue;
                     if (nj > start && align_up(t) + it.job.ntiles > kLaunchBlocks) {
                         launches.push_back({start, nj - start, (uint32_t)t, f, kind});
                         start = nj;

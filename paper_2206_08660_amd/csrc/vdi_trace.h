@@ -773,6 +773,19 @@ VDI_HD inline bool cell_occupied(const DevVDI &V, int cell)
     return (VDI_LOAD(V.gbits + ((uint32_t)cell >> 5), 1) >> ((uint32_t)cell & 31u)) & 1u;
 }
 
+// "over" of a front and a back partial result of one ray.
+VDI_HD inline Accum over(const Accum &f, const Accum &b)
+{
+    return {fmaf(f.T, b.r, f.r), fmaf(f.T, b.g, f.g), fmaf(f.T, b.b, f.b), f.T * b.T};
+}
+
+// `pre`, the parts of a ray so far in ray order, with the next one, unless the
+// ray has terminated.
+VDI_HD inline void append(Accum &pre, const Accum &a)
+{
+    if (pre.T > kTTerm) pre = over(pre, a);
+}
+
 // ---------------------------------------------------------------------------
 // Exact render (Sections 4.1-4.3)
 // ---------------------------------------------------------------------------
@@ -790,19 +803,24 @@ VDI_HD inline bool cell_occupied(const DevVDI &V, int cell)
 // supersegment on both sides of it composite to the whole piece's colour and
 // opacity (Eq. 2 is multiplicative in the length), so the parts, combined in
 // ray order, give the whole ray up to rounding.
-template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx = uint64_t>
+//
+// FOLD: all the parts one after another on one lane, each from full
+// transmittance and combined by split_tile's operations in split_tile's order:
+// the same image, bit for bit.
+template <int FMT, int SEARCH, bool ESS, bool COUNT, typename Idx = uint64_t, bool FOLD = false>
 VDI_HDI void trace_exact_part(const DevVDI &V, const Frame &F, const float *s_gz, int px, int py, int part, int parts,
                               Accum &A, Counters &cnt)
 {
     Ray r;
     const double xc = pixel_ndc(px, F.W, F.inv_w), yc = pixel_ndc(py, F.H, F.inv_h);
     if (!ray_setup(F, xc, yc, r)) return;
-    if (parts > 1) {
-        const double z0 = F.Z0 + r.t0 * r.Zp, z1 = F.Z0 + r.t1 * r.Zp, t0 = r.t0, span = r.t1 - r.t0;
-        auto cut = [&](int k) { return t0 + span * ((k * z0) * rcp64(parts * z1 - k * (z1 - z0))); };
-        if (part > 0) r.t0 = cut(part);
-        if (part + 1 < parts) r.t1 = cut(part + 1);
-    }
+    // Where part k begins; k = parts: where the last one ends.
+    auto cut = [&](int k) {
+        if (k == 0) return r.t0;
+        if (k == parts) return r.t1;
+        const double z0 = F.Z0 + r.t0 * r.Zp, z1 = F.Z0 + r.t1 * r.Zp;
+        return r.t0 + (r.t1 - r.t0) * ((k * z0) * rcp64(parts * z1 - k * (z1 - z0)));
+    };
     const int WO = V.WO, HO = V.HO, gk = V.gk;
     // Direction of travel across the list grid: d/dt (X/Z) has the sign of Kx.
     const double Kx = r.Xp * F.Z0 - F.X0 * r.Zp, Ky = r.Yp * F.Z0 - F.Y0 * r.Zp;
@@ -810,7 +828,7 @@ VDI_HDI void trace_exact_part(const DevVDI &V, const Frame &F, const float *s_gz
     const bool fwd = r.Zp >= 0.0, flat = fabs(r.Zp) < kFlatZ;
     const double inf = __builtin_huge_val();
     const double invZp = flat ? 0.0 : rcp64(r.Zp);
-    double t = r.t0, tx = inf, ty = inf, tz = inf;
+    double t, tend, tx = inf, ty = inf, tz = inf;  // tend: the part's end
     // (ix, iy): current list; the next x (y) grid line crossed is ix + (sx > 0).
     int ix = 0, iy = 0, cz = 0;
     const int ox = sx > 0, oy = sy > 0;
@@ -835,9 +853,6 @@ VDI_HDI void trace_exact_part(const DevVDI &V, const Frame &F, const float *s_gz
             tz = slice_t(cz);
         }
     };
-    locate(t);
-    int p = -1;
-    int n = VDI_LOAD(elem(V.count, (Idx)((Idx)iy * (Idx)WO + (Idx)ix)), 0);
     // Every iteration moves one list or jumps a grid cell; the cap only
     // guards against a loop that does not advance.
     const int max_iter = 4 * (WO + HO) + 4 * V.gnz + 64;
@@ -852,98 +867,119 @@ VDI_HDI void trace_exact_part(const DevVDI &V, const Frame &F, const float *s_gz
         const int m = sy > 0 ? min((c + 1) * gk, HO) : c * gk;
         return (m > 0 && m < HO) ? line_t(m, V.dcy, F.Y0, r.Yp, F.Z0, r.Zp) : inf;
     };
-    // Cell mode (empty-space skipping): one empty grid cell per iteration, a
-    // crossing and a grid load, no division; lanes in cell mode and in list
-    // mode advance together.  Where a non-empty cell is entered the ray is
-    // located again and walks lists.
-    bool cellmode = false;
-    for (int it = 0; it < max_iter; ++it) {
-        VDI_STEP();
-        if constexpr (ESS) {
-            if (cellmode) {
-                const double te = fmin(fmin(tx, ty), fmin(tz, r.t1));
-                if (te >= r.t1) break;
-                // One crossing solve per step whichever face the lanes leave by.
-                const bool ax = tx <= ty && tx <= tz, ay = !ax && ty <= tz, az = !ax && !ay;
-                ix += ax ? sx : 0;
-                iy += ay ? sy : 0;
-                cz += az ? (fwd ? 1 : -1) : 0;
-                const int cc = ax ? ix : iy, sc = ax ? sx : sy, lim = ax ? WO : HO;
-                const int m = sc > 0 ? min((cc + 1) * gk, lim) : cc * gk;
-                const double tl = (sc != 0 && m > 0 && m < lim && !az)
-                                      ? line_t(m, ax ? V.dcx : V.dcy, ax ? F.X0 : F.Y0, ax ? r.Xp : r.Yp, F.Z0, r.Zp)
-                                      : inf;
-                const double tzn = az ? slice_t(cz) : tz;
-                tx = ax ? tl : tx;
-                ty = ay ? tl : ty;
-                tz = tzn;
-                if ((unsigned)ix >= (unsigned)V.GW || (unsigned)iy >= (unsigned)V.GH || (unsigned)cz >= (unsigned)V.gnz)
-                    break;
-                t = fmax(t, te);
-                const int cell = (cz * V.GH + iy) * V.GW + ix;
-                if (cell_occupied(V, cell)) {
-                    cellmode = false;
-                    locate(t);
-                    n = VDI_LOAD(elem(V.count, (Idx)((Idx)iy * (Idx)WO + (Idx)ix)), 0);
-                    ccell = -1;
-                }
-                continue;
-            }
-        }
-        const double tn = fmin(fmin(tx, ty), r.t1);
-        if constexpr (ESS) {
-            while (tz <= t) {
-                cz += fwd ? 1 : -1;
-                tz = slice_t(cz);
-            }
-            const int cx = (int)((float)ix * V.inv_gk), cy = (int)((float)iy * V.inv_gk);
-            const int cell = (cz * V.GH + cy) * V.GW + cx;
-            if (cell != ccell) {
-                cg = cell_occupied(V, cell);
-                ccell = cell;
-            }
-            if (!cg) {
-                // Empty-space skipping: switch to walking cells (ix, iy become
-                // the cell indices, tx, ty the crossings of cell boundaries)
-                // when that skips a list, i.e. the ray leaves its list before
-                // the cell: otherwise the list step below reaches the list's
-                // exit in one step where cells would take one per depth
-                // slice.  Not either when the ray sits on the cell's exit (a
-                // located position rounded onto a cell boundary): then the
-                // list step moves it across.
-                const double ctx = cell_tx(cx), cty = cell_ty(cy);
-                const double te = fmin(fmin(ctx, cty), fmin(tz, r.t1));
-                if (te > t && tn < te) {
-                    ix = cx;
-                    iy = cy;
-                    tx = ctx;
-                    ty = cty;
-                    cellmode = true;
+    Accum pre = {0.0f, 0.0f, 0.0f, 1.0f};  // FOLD: the parts before this one
+    bool again = false;                    // FOLD: this part is walked on top of them
+    for (int k = FOLD ? 0 : part;;) {
+        t = cut(k);
+        tend = cut(k + 1);
+        locate(t);
+        ccell = -1;
+        int p = -1;
+        int n = VDI_LOAD(elem(V.count, (Idx)((Idx)iy * (Idx)WO + (Idx)ix)), 0);
+        // Cell mode (empty-space skipping): one empty grid cell per iteration, a
+        // crossing and a grid load, no division; lanes in cell mode and in list
+        // mode advance together.  Where a non-empty cell is entered the ray is
+        // located again and walks lists.
+        bool cellmode = false;
+        for (int it = 0; it < max_iter; ++it) {
+            VDI_STEP();
+            if constexpr (ESS) {
+                if (cellmode) {
+                    const double te = fmin(fmin(tx, ty), fmin(tz, tend));
+                    if (te >= tend) break;
+                    // One crossing solve per step whichever face the lanes leave by.
+                    const bool ax = tx <= ty && tx <= tz, ay = !ax && ty <= tz, az = !ax && !ay;
+                    ix += ax ? sx : 0;
+                    iy += ay ? sy : 0;
+                    cz += az ? (fwd ? 1 : -1) : 0;
+                    const int cc = ax ? ix : iy, sc = ax ? sx : sy, lim = ax ? WO : HO;
+                    const int m = sc > 0 ? min((cc + 1) * gk, lim) : cc * gk;
+                    const double tl = (sc != 0 && m > 0 && m < lim && !az)
+                                          ? line_t(m, ax ? V.dcx : V.dcy, ax ? F.X0 : F.Y0, ax ? r.Xp : r.Yp, F.Z0, r.Zp)
+                                          : inf;
+                    const double tzn = az ? slice_t(cz) : tz;
+                    tx = ax ? tl : tx;
+                    ty = ay ? tl : ty;
+                    tz = tzn;
+                    if ((unsigned)ix >= (unsigned)V.GW || (unsigned)iy >= (unsigned)V.GH || (unsigned)cz >= (unsigned)V.gnz)
+                        break;
+                    t = fmax(t, te);
+                    const int cell = (cz * V.GH + iy) * V.GW + ix;
+                    if (cell_occupied(V, cell)) {
+                        cellmode = false;
+                        locate(t);
+                        n = VDI_LOAD(elem(V.count, (Idx)((Idx)iy * (Idx)WO + (Idx)ix)), 0);
+                        ccell = -1;
+                    }
                     continue;
                 }
             }
+            const double tn = fmin(fmin(tx, ty), tend);
+            if constexpr (ESS) {
+                while (tz <= t) {
+                    cz += fwd ? 1 : -1;
+                    tz = slice_t(cz);
+                }
+                const int cx = (int)((float)ix * V.inv_gk), cy = (int)((float)iy * V.inv_gk);
+                const int cell = (cz * V.GH + cy) * V.GW + cx;
+                if (cell != ccell) {
+                    cg = cell_occupied(V, cell);
+                    ccell = cell;
+                }
+                if (!cg) {
+                    // Empty-space skipping: switch to walking cells (ix, iy become
+                    // the cell indices, tx, ty the crossings of cell boundaries)
+                    // when that skips a list, i.e. the ray leaves its list before
+                    // the cell: otherwise the list step below reaches the list's
+                    // exit in one step where cells would take one per depth
+                    // slice.  Not either when the ray sits on the cell's exit (a
+                    // located position rounded onto a cell boundary): then the
+                    // list step moves it across.
+                    const double ctx = cell_tx(cx), cty = cell_ty(cy);
+                    const double te = fmin(fmin(ctx, cty), fmin(tz, tend));
+                    if (te > t && tn < te) {
+                        ix = cx;
+                        iy = cy;
+                        tx = ctx;
+                        ty = cty;
+                        cellmode = true;
+                        continue;
+                    }
+                }
+            }
+            // The list entered next, and its count, are known before this one is composited.
+            const bool stepx = tx <= ty;
+            const int nx = stepx ? ix + sx : ix, ny = stepx ? iy : iy + sy;
+            const bool more = tn < tend && (unsigned)nx < (unsigned)WO && (unsigned)ny < (unsigned)HO;
+            const int n_next = more ? VDI_LOAD(elem(V.count, (Idx)((Idx)ny * (Idx)WO + (Idx)nx)), 0) : 0;
+            if (tn > t && do_list<FMT, SEARCH, COUNT, Idx>(V, F, ix, iy, n, t, tn, F.Z0, r.Zp, invZp, A, p, cnt)) break;
+            if (!more) break;
+            {
+                // One crossing solve per step, for the axis the ray stepped in.
+                const int mm = stepx ? nx + ox : ny + oy, lim = stepx ? WO : HO;
+                const double tl = (mm > 0 && mm < lim)
+                                      ? line_t(mm, stepx ? V.dcx : V.dcy, stepx ? F.X0 : F.Y0, stepx ? r.Xp : r.Yp, F.Z0, r.Zp)
+                                      : inf;
+                tx = stepx ? tl : tx;
+                ty = stepx ? ty : tl;
+            }
+            ix = nx;
+            iy = ny;
+            n = n_next;
+            t = fmax(t, tn);
         }
-        // The list entered next, and its count, are known before this one is composited.
-        const bool stepx = tx <= ty;
-        const int nx = stepx ? ix + sx : ix, ny = stepx ? iy : iy + sy;
-        const bool more = tn < r.t1 && (unsigned)nx < (unsigned)WO && (unsigned)ny < (unsigned)HO;
-        const int n_next = more ? VDI_LOAD(elem(V.count, (Idx)((Idx)ny * (Idx)WO + (Idx)nx)), 0) : 0;
-        if (tn > t && do_list<FMT, SEARCH, COUNT, Idx>(V, F, ix, iy, n, t, tn, F.Z0, r.Zp, invZp, A, p, cnt)) break;
-        if (!more) break;
-        {
-            // One crossing solve per step, for the axis the ray stepped in.
-            const int mm = stepx ? nx + ox : ny + oy, lim = stepx ? WO : HO;
-            const double tl = (mm > 0 && mm < lim)
-                                  ? line_t(mm, stepx ? V.dcx : V.dcy, stepx ? F.X0 : F.Y0, stepx ? r.Xp : r.Yp, F.Z0, r.Zp)
-                                  : inf;
-            tx = stepx ? tl : tx;
-            ty = stepx ? ty : tl;
+        if (!FOLD || parts == 1 || again) return;
+        if (k > 0 && pre.T * A.T <= kTTerm) {
+            // The ray ends inside this part: once more, on top of those before.
+            A = pre;
+            again = true;
+            continue;
         }
-        ix = nx;
-        iy = ny;
-        n = n_next;
-        t = fmax(t, tn);
+        append(pre, A);
+        if (++k == parts || !(pre.T > kTTerm)) break;
+        A = {0.0f, 0.0f, 0.0f, 1.0f};
     }
+    A = pre;
 }
 
 VDI_HD inline float4 to_rgba(const Accum &A) { return make_float4(A.r, A.g, A.b, 1.0f - A.T); }
@@ -1240,19 +1276,6 @@ VDI_HDI Accum trace_preview(const DevVDI &V, const Frame &F, const float *s_gz, 
         }
     }
     return A;
-}
-
-// "over" of a front and a back partial result of one ray.
-VDI_HD inline Accum over(const Accum &f, const Accum &b)
-{
-    return {fmaf(f.T, b.r, f.r), fmaf(f.T, b.g, f.g), fmaf(f.T, b.b, f.b), f.T * b.T};
-}
-
-// `pre`, the parts of a ray so far in ray order, with the next one, unless the
-// ray has terminated.
-VDI_HD inline void append(Accum &pre, const Accum &a)
-{
-    if (pre.T > kTTerm) pre = over(pre, a);
 }
 
 // Combine the partial results of the `parts` lanes of each ray (adjacent
