@@ -67,11 +67,20 @@ inline int exact_parts(int w, int h, double lists)
 // 411; 24 1560 / 1668, 633 / 486; 32 2074 / 1861, 852 / 621; 64 4164 / 3323,
 // 1754 / 1109; of 256 x 256 4 865 / 1366, 234 / 273; 6 1254 / 1563, 327 / 315; 8
 // 1644 / 1659, 422 / 363; 16 3218 / 3047, 809 / 661.  Rays in one part would
-// take 3156 and 719 for the 64: a cut costs about as much as a list.
+// take 3156 and 719 for the 64: a cut costs about as much as a list.  Beside
+// `others` rays of other frames, split rays share their launch, and folded ones
+// have one of their own: 4 exact frames of 512 x 360 at up to 30 deg and 8
+// previews (737k rays, 230k others) 1170 / 1507, 471 / 474 (1080p VDI); a
+// server's 12 exact frames of up to 384 x 256 and 6 previews (850k, 147k) 1514 /
+// 1644, 667 / 713, of up to 512 x 360 (1.6M, 276k) 2540 / 2228.
 #ifndef VDI_SPLIT_RAYS
-#define VDI_SPLIT_RAYS 393216
+#define VDI_SPLIT_RAYS 393216.0
 #endif
-inline bool split_launch(double rays) { return rays <= VDI_SPLIT_RAYS; }
+inline bool split_launch(double rays, double others)
+{
+    const double most = VDI_SPLIT_RAYS + 4.0 * others;
+    return rays <= (most < 1e6 ? most : 1e6);
+}
 // An exact wavefront renders 64 / parts rays, at most kXTileH rows tall; the
 // `parts` lanes of a ray are adjacent.
 __host__ __device__ inline void exact_tile_dims(int parts, int &tw, int &th)

@@ -55,8 +55,6 @@ constexpr int kMaxBatch = 256;                 // requests per batch
 #define VDI_BATCH_TILES ((1ull << 23) / (kTileW * kTileH))
 #endif
 constexpr uint64_t kBatchTiles = VDI_BATCH_TILES;
-// Rays in parts of a frame (split_launch).
-double part_rays(bool preview, const Frame &f) { return !preview && f.xparts > 1 ? (double)f.W * f.H : 0.0; }
 // Settle how an exact job's rays in parts are walked in its launch.
 void place_parts(BatchJob &job, bool split)
 {
@@ -88,6 +86,12 @@ struct Lane {
     UpsampleJob *h_up = nullptr, *d_up = nullptr;
     std::vector<uint64_t> tickets;
     bool busy = false;
+};
+
+// Rays of a launch's frames (split_launch).
+struct LaunchRays {
+    double parts = 0.0, others = 0.0;
+    void add(bool preview, const Frame &f, double n = 1.0) { (!preview && f.xparts > 1 ? parts : others) += n * f.W * f.H; }
 };
 
 // Persistent engine (vdi_server_create_persistent): one resident launch of
@@ -130,7 +134,7 @@ struct Persist {
     uint64_t tiles = 0;                                // global tiles given out by it
     uint64_t mem_epoch = 0;                            // g_mem_epoch at its start
     std::vector<uint64_t> published;                   // its tickets not yet retired
-    double rays = 0.0;                                 // ... and their rays in parts (part_rays)
+    LaunchRays rays;                                   // ... and their rays
     std::chrono::steady_clock::time_point idle_since;
 };
 
@@ -191,10 +195,10 @@ void launch_batch(vdi_server_s *s, Lane &L)
         take.push_back(s->queue.front());
         s->queue.pop_front();
     }
-    double rays = 0.0;
-    for (uint64_t tk : take) rays += part_rays(s->requests.at(tk).preview, s->requests.at(tk).job.F);
+    LaunchRays rays;
+    for (uint64_t tk : take) rays.add(s->requests.at(tk).preview, s->requests.at(tk).job.F);
     for (uint64_t tk : take)
-        if (!s->requests.at(tk).preview) place_parts(s->requests.at(tk).job, split_launch(rays));
+        if (!s->requests.at(tk).preview) place_parts(s->requests.at(tk).job, split_launch(rays.parts, rays.others));
     // Job tables: one group per format, exact frames before previews, and one
     // for its folded frames, each sorted by tile0.
     int nj = 0, nu = 0;
@@ -324,8 +328,9 @@ void persist_pump(vdi_server_s *s)
         Request &r = s->requests.at(tk);
         if (!P.running) persist_launch(s, r.fmt);
         if (s->err) return;
-        const double rays = part_rays(r.preview, r.job.F);
-        if (!r.preview) place_parts(r.job, split_launch(P.rays + rays));
+        LaunchRays rays = P.rays;
+        rays.add(r.preview, r.job.F);
+        if (!r.preview) place_parts(r.job, split_launch(rays.parts, 0.0));
         const uint64_t t0 = align_up(P.tiles);
         const uint64_t u0 = align_up(t0 + r.job.ntiles);
         const uint64_t end = r.down ? u0 + r.up.ntiles : t0 + r.job.ntiles;
@@ -357,7 +362,7 @@ void persist_pump(vdi_server_s *s)
         __atomic_store_n(&P.h_ctl->tail.v, (unsigned long long)(j + 1), __ATOMIC_RELEASE);
         s->queue.pop_front();
         P.published.push_back(tk);
-        P.rays += rays;
+        P.rays = rays;
         s->st.queued = (int32_t)s->queue.size();
     }
 }
@@ -370,7 +375,7 @@ bool persist_retire(vdi_server_s *s)
     for (size_t i = 0; i < P.published.size();) {
         const uint64_t tk = P.published[i];
         if (__atomic_load_n(&P.h_done[s->requests.at(tk).slot], __ATOMIC_ACQUIRE) != 0u) {
-            P.rays -= part_rays(s->requests.at(tk).preview, s->requests.at(tk).job.F);
+            P.rays.add(s->requests.at(tk).preview, s->requests.at(tk).job.F, -1.0);
             finish_request(s, tk);
             P.published[i] = P.published.back();
             P.published.pop_back();
@@ -732,7 +737,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
     if (!vdis || !cams || !widths || !heights || !D_I || !D_R || !outs) return set_error(VDI_ERR_ARG, "null array");
     std::vector<BatchItem> items((size_t)n);
     bool wide = false;
-    double rays = 0.0;
+    LaunchRays rays;
     int device = -1;
     for (int i = 0; i < n; ++i) {
         int rc = check_render_args(vdis[i], &cams[i], widths[i], heights[i], D_I[i], D_R[i], outs[i]);
@@ -755,7 +760,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         it.fmt = S.dev.fmt;
         it.preview = D_R[i] > 0.0f;
         it.down = (w != widths[i] || h != heights[i]);
-        rays += part_rays(it.preview, it.job.F);
+        rays.add(it.preview, it.job.F);
         if (it.preview) it.job.ntiles = preview_tiles(w, h);
         if (it.down) {
             // Rounded up to a power of two (at least 1 MiB), as for vdi_render.
@@ -768,7 +773,7 @@ int render_batch(int32_t n, const vdi_t *vdis, const vdi_camera *cams, const int
         }
     }
     for (BatchItem &it : items)
-        if (!it.preview) place_parts(it.job, split_launch(rays));
+        if (!it.preview) place_parts(it.job, split_launch(rays.parts, rays.others));
     hipError_t e = hipSetDevice(device);
     if (e != hipSuccess) return hip_error(e, "hipSetDevice");
     hipMemPool_t pool = nullptr;

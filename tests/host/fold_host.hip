@@ -26,4 +26,4 @@ extern "C" int host_fold(const vdi_desc *d, const uint32_t *grid, const vdi_came
     return 0;
 }
 
-extern "C" int host_split_launch(double rays) { return vdi::split_launch(rays); }
+extern "C" int host_split_launch(double rays, double others) { return vdi::split_launch(rays, others); }

@@ -30,7 +30,7 @@ def host(tmp_path_factory):
     L = ctypes.CDLL(out)
     P, I = ctypes.c_void_p, ctypes.c_int
     L.host_fold.argtypes = [ctypes.POINTER(V.Desc), P, ctypes.POINTER(V.Camera), I, I, I, I, P, P]
-    L.host_split_launch.argtypes = [ctypes.c_double]
+    L.host_split_launch.argtypes = [ctypes.c_double, ctypes.c_double]
     return L
 
 
@@ -51,5 +51,9 @@ def test_folded_rays_are_split_rays(host, theta, alpha_max, ess):
 
 
 def test_launches_that_split_rays(host):
-    assert host.host_split_launch(128 * 128) and host.host_split_launch(512 * 512) and host.host_split_launch(24 * 128 * 128)
-    assert not host.host_split_launch(32 * 128 * 128) and not host.host_split_launch(8 * 256 * 256)
+    f = lambda rays, others=0: bool(host.host_split_launch(rays, others))
+    assert f(128 * 128) and f(512 * 512) and f(24 * 128 * 128) and f(4 * 256 * 256)
+    assert not f(32 * 128 * 128) and not f(8 * 256 * 256)
+    # Beside other frames, up to a million rays.
+    assert f(4 * 512 * 360, 230_000) and f(850_000, 147_000) and not f(1_600_000, 276_000)
+    assert not f(64 * 128 * 128, 10_000_000)

@@ -196,14 +196,14 @@ def test_dvr_of_volumes_with_values_out_of_range(dims, tf, values):
         assert fin.any() and all(same.values()) and off <= 1e-4, precision
 
 
-# 30 frames of 128 x 128 and 8 of 97 x 55 to 300 x 217: more rays in parts than split_launch splits.
+# 70 frames of 128 x 128 and 8 of 97 x 55 to 300 x 216: more rays in parts than a launch splits.
 @pytest.mark.parametrize("store", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("alpha_max", [0.12, 0.95])
 def test_many_small_frames_are_their_single_renders(store, alpha_max):
     V = _V()
     from paper_2206_08660_amd import serve as S
     v = synth.random_vdi(131, 97, 24, seed=84, alpha_max=alpha_max, empty_frac=0.3)
-    frames = [(inputs.orbit_camera(-44.0 + 3.0 * i), 128, 128, 1.0, 0.0) for i in range(30)]
+    frames = [(inputs.orbit_camera(-44.0 + 1.2 * i), 128, 128, 1.0, 0.0) for i in range(70)]
     frames += [(inputs.orbit_camera(7.0 * i - 20.0), 97 + 29 * i, 55 + 23 * i, 1.0, 0.0) for i in range(8)]
     frames += [(inputs.orbit_camera(11.0), 640, 480, 1.0, 0.0), (inputs.orbit_camera(12.0), 256, 256, 2.0, 0.0),
                (inputs.orbit_camera(-9.0), 200, 150, 1.0, 2.0), (inputs.orbit_camera(31.0), 320, 200, 2.0, 1.0)]
@@ -220,7 +220,7 @@ def test_many_small_frames_are_their_single_renders(store, alpha_max):
         for persistent in (False, True):
             print(f"[gpu] server, persistent {persistent}, {store}, alpha {alpha_max}", flush=True)
             got = outs()
-            with S.Server(4 << 30, max_inflight=64, persistent=persistent) as s:
+            with S.Server(4 << 30, max_inflight=96, persistent=persistent) as s:
                 for (cam, w, hh, di, dr), o in zip(frames, got):
                     assert s.submit(h, cam, w, hh, di, dr, o) is not None
                 s.drain()
