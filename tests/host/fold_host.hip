@@ -1,4 +1,5 @@
-// Host build of rays folded on one lane.
+// Host build of rays folded on one lane, of the order of a frame's tiles and of
+// 32-bit plane offsets.
 #include "split_host.hip"
 
 // The exact frame with its rays in `parts` parts: folded into `folded`, and part
@@ -24,6 +25,41 @@ extern "C" int host_fold(const vdi_desc *d, const uint32_t *grid, const vdi_came
             memcpy(split + 4 * ((size_t)py * W + px), &s, sizeof s);
         }
     return 0;
+}
+
+// host_tiles with the order as an argument.
+extern "C" void host_tiles_order(int W, int H, const int *r, int tw, int th, int band, int middle_out, int *placed)
+{
+    vdi::Frame f = {};
+    f.W = W;
+    f.H = H;
+    f.rx0 = r[0];
+    f.ry0 = r[1];
+    f.rx1 = r[2];
+    f.ry1 = r[3];
+    const int nx = (W + tw - 1) / tw, n = nx * ((H + th - 1) / th);
+    for (int i = 0; i < n; ++i) {
+        int x0 = -1, y0 = -1;
+        const bool meets = vdi::place_tile(f, tw, th, band, i, x0, y0, middle_out != 0);
+        if (x0 < 0 || y0 < 0 || x0 >= W || y0 >= H || x0 % tw || y0 % th) continue;
+        placed[(y0 / th) * nx + x0 / tw] += meets ? 100 : 101;
+    }
+}
+
+// Whether a VDI of these sizes is rendered with 32-bit offsets; the largest
+// element offset of a slot in 32 and in 64 bits, and the plane's elements.
+extern "C" int host_fits32(int WO, int HO, int NS, uint64_t *o)
+{
+    o[0] = o[1] = 0;
+    for (int iy = HO > 2 ? HO - 2 : 0; iy < HO; ++iy)
+        for (int ix = WO > 2 ? WO - 2 : 0; ix < WO; ++ix) {
+            const uint32_t a = vdi::list_base_xy<uint32_t>(ix, iy, NS, WO) + (uint32_t)(NS - 1) * vdi::kBrick;
+            const uint64_t b = vdi::list_base_xy<uint64_t>(ix, iy, NS, WO) + (uint64_t)(NS - 1) * vdi::kBrick;
+            o[0] = std::max<uint64_t>(o[0], a);
+            o[1] = std::max(o[1], b);
+        }
+    o[2] = vdi::plane_elems(WO, HO, NS);
+    return vdi::fits32(WO, HO, NS);
 }
 
 extern "C" int host_split_launch(double rays, double others) { return vdi::split_launch(rays, others); }

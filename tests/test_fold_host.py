@@ -1,5 +1,6 @@
 """Exact rays in parts folded on one lane, on the host (hipcc; nothing runs on a
-GPU): bit for bit what the parts on a lane each combine to."""
+GPU): bit for bit what the parts on a lane each combine to; every tile placed
+once in both orders; the line between 32- and 64-bit plane offsets."""
 import ctypes
 import os
 import shutil
@@ -30,6 +31,8 @@ def host(tmp_path_factory):
     L = ctypes.CDLL(out)
     P, I = ctypes.c_void_p, ctypes.c_int
     L.host_fold.argtypes = [ctypes.POINTER(V.Desc), P, ctypes.POINTER(V.Camera), I, I, I, I, P, P]
+    L.host_tiles_order.argtypes = [I, I, P, I, I, I, I, P]
+    L.host_fits32.argtypes = [I, I, I, ctypes.POINTER(ctypes.c_uint64)]
     L.host_split_launch.argtypes = [ctypes.c_double, ctypes.c_double]
     return L
 
@@ -48,6 +51,40 @@ def test_folded_rays_are_split_rays(host, theta, alpha_max, ess):
                 assert host.host_fold(ctypes.byref(d), grid.ctypes.data, ctypes.byref(V.camera(inputs.orbit_camera(theta))),
                                       W, H, parts, ess, folded.ctypes.data, split.ctypes.data) == 0
                 assert np.array_equal(folded, split)
+
+
+@pytest.mark.parametrize("middle_out", [0, 1])
+def test_every_tile_is_placed_once_in_either_order(host, middle_out):
+    rng = np.random.default_rng(9)
+    sizes = [(1, 260)] * 250 + [(600, 1400)] * 8
+    for k, (lo, hi) in enumerate(sizes):
+        W, H = (int(x) for x in rng.integers(lo, hi, 2))
+        tw, th = (1 << int(x) for x in rng.integers(0 if lo == 1 else 1, 5 if lo == 1 else 4, 2))
+        r = np.array([*(rng.integers(0, n + 1) for n in (W, H, W, H))], np.int32)
+        if lo > 1 or rng.random() < 0.2:
+            r[:] = 0, 0, W, H
+        nx, ny = -(-W // tw), -(-H // th)
+        placed = np.zeros(nx * ny, np.int32)
+        host.host_tiles_order(W, H, r.ctypes.data, tw, th, int(rng.integers(1, 9)), middle_out, placed.ctypes.data)
+        assert set(placed) <= {100, 101}, (W, H, r, tw, th)
+        x, y = np.meshgrid(np.arange(nx) * tw, np.arange(ny) * th)
+        meets = (x < r[2]) & (x + tw > r[0]) & (y < r[3]) & (y + th > r[1]) & (r[2] > r[0]) & (r[3] > r[1])
+        assert (placed.reshape(ny, nx)[meets] == 100).all()
+
+
+def test_offsets_fit_32_bits_up_to_4_gib_of_colours(host):
+    o = (ctypes.c_uint64 * 3)()
+    seen = set()
+    for WO, HO, NS in [(1, 1, 1), (1920, 1080, 50), (1280, 720, 255), (1281, 822, 255), (32768, 8192, 1), (32768, 8190, 1),
+                       (32767, 8191, 1), (16384, 16383, 1), (2049, 2047, 64), (2049, 2047, 63), (32768, 32768, 255)]:
+        fits = host.host_fits32(WO, HO, NS, o)
+        padded = (WO + 1) // 2 * 2 * ((HO + 1) // 2 * 2) * NS
+        assert o[2] == padded and fits == (padded * 16 <= 2 ** 32 - 1)
+        assert o[1] < padded
+        if fits:   # byte offsets of the largest elements, colours, do not wrap
+            assert o[0] == o[1] and o[1] * 16 + 15 < 2 ** 32
+        seen.add(bool(fits))
+    assert seen == {True, False}
 
 
 def test_launches_that_split_rays(host):

@@ -2,7 +2,7 @@
 far from the volume; device planes that are not memory of the device or not
 aligned to a slot, or are still being written on the null stream; volumes with
 infinite and NaN voxels; so many small exact frames at once that their rays'
-parts are folded on one lane."""
+parts are folded on one lane; a VDI too large for 32-bit offsets."""
 import ctypes
 
 import numpy as np
@@ -226,3 +226,38 @@ def test_many_small_frames_are_their_single_renders(store, alpha_max):
                 s.drain()
             torch.cuda.synchronize()
             assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("store", ["f32", "f16", "bf16"])
+def test_a_vdi_too_large_for_32_bit_offsets(store):
+    """The same lists with N_S 20 and with N_S 255 (over 2^28 slots, which the kernels address in 64 bits), bit for
+    bit: single and batched frames, whole, split and folded rays, previews."""
+    V = _V()
+    tile = synth.random_vdi(161, 104, 20, seed=85, alpha_max=0.2, empty_frac=0.2)
+    count, depth, rgba = (np.tile(a, (8, 8) if a.ndim == 2 else (1, 8, 8, 1)) for a in (tile.count, tile.depth, tile.rgba))
+    small = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (count, depth, rgba)]
+    big = [small[0]] + [torch.zeros((255, *t.shape[1:]), device="cuda") for t in small[1:]]
+    for b, t in zip(big[1:], small[1:]):
+        b[:20] = t
+    rest = (tile.camera, tile.bmin, tile.bmax, tile.grid_k, tile.grid_nz, tile.grid_z)
+    exact = [(inputs.orbit_camera(a), w, hh, 1.0, 0.0) for a, w, hh in ((8.0, 128, 128), (31.0, 900, 600), (-20.0, 60, 41))]
+    previews = [(inputs.orbit_camera(a), 800, 450, di, dr) for a, di, dr in ((8.0, 1.0, 1.0), (-31.0, 2.0, 2.0))]
+    many = [(inputs.orbit_camera(0.5 * i), 128, 128, 1.0, 0.0) for i in range(30)]
+    images = []
+    for planes in (small, big):
+        with V.Vdi(V.DeviceVDI(*planes, *rest), store=store) as h:
+            got = [h.render(f[0], f[1], f[2], d_i=f[3], d_r=f[4]) for f in exact + previews + many]
+            got.append(h.render(*exact[1][:3], ess=False))
+            got.append(h.render(*exact[0][:3], ess=False))
+            for frames in (exact[:1], exact[1:2], exact + previews, previews, many):
+                outs = [torch.full((f[2], f[1], 4), -1.0, device="cuda") for f in frames]
+                V.render_batch([(h, *f, o) for f, o in zip(frames, outs)])
+                got += outs
+            torch.cuda.synchronize()
+            print(f"[gpu] {store}, N_S {h.ns}: {len(got)} images", flush=True)
+        images.append([g.cpu() for g in got])
+    assert all(torch.equal(a, b) for a, b in zip(*images))
+    singles = dict(zip(map(id, exact + previews + many), images[1]))
+    batched = images[1][len(singles) + 2:]
+    for f, b in zip(exact[:1] + exact[1:2] + exact + previews + previews + many, batched):
+        assert torch.equal(singles[id(f)], b)
