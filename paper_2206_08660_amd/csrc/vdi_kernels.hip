@@ -78,11 +78,20 @@ __device__ __forceinline__ void store_px(float4 *p, float4 v)
 // and leave without setting up their rays, which takes about as long as 20
 // list steps (1080p workload: two tiles in three; 32,000 of them take 40 us).
 // They come last.  The tiles that meet the AABB are dealt to the XCDs in bands
-// of `band` tile rows (xcd_tile).
-VDI_HDI bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &x0, int &y0, bool middle_out = false)
+// of `band` tile rows (xcd_tile).  Exact frames whose tiles are all in flight at
+// once (kMiddleOut) gain nothing by it, and lose where the long tiles, pulled
+// together, crowd: they keep all tiles in the image's order (600 x 500 at 20 and
+// 40 deg, us, AABB first / image's order: 900 x 600 / N_S 30 VDI 500, 1043 / 488,
+// 1032; 1280 x 720 / N_S 20 649, 1362 / 639, 1286; 1920 x 1080 / N_S 50 512, 950 /
+// 538, 974).
+VDI_HDI bool place_tile(const Frame &F, int tw, int th, int band, int bid, int &x0, int &y0, bool middle_out = false,
+                        bool exact = false)
 {
     const int tiles_x = (F.W + tw - 1) / tw, tiles_y = (F.H + th - 1) / th;
-    const int cx0 = F.rx0 / tw, cx1 = (F.rx1 + tw - 1) / tw, cy0 = F.ry0 / th, cy1 = (F.ry1 + th - 1) / th;
+    // Placed as if all tiles met it.
+    const bool all = exact && tiles_x * tiles_y <= kMiddleOut;
+    const int cx0 = all ? 0 : F.rx0 / tw, cx1 = all ? tiles_x : (F.rx1 + tw - 1) / tw;
+    const int cy0 = all ? 0 : F.ry0 / th, cy1 = all ? tiles_y : (F.ry1 + th - 1) / th;
     const int nx = max(cx1 - cx0, 0), ny = nx > 0 ? max(cy1 - cy0, 0) : 0, inside = nx * ny;
     if (bid < inside) {
         const int t = xcd_tile(bid, nx, ny, band, middle_out);
@@ -111,7 +120,7 @@ template <int FMT, int SEARCH, bool ESS, typename Idx, bool WT = false, bool FOL
 __device__ __forceinline__ void exact_tile(const DevVDI &V, const Frame &F, const float *s_gz, int tile_index)
 {
     int x0, y0;
-    const bool meets = place_tile(F, kXTileW, kXTileH, kXBandRows, tile_index, x0, y0);
+    const bool meets = place_tile(F, kXTileW, kXTileH, kXBandRows, tile_index, x0, y0, false, true);
     const int px = x0 + (int)threadIdx.x % kXTileW, py = y0 + (int)threadIdx.x / kXTileW;
     if (px >= F.W || py >= F.H) return;
     float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);

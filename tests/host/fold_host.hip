@@ -27,8 +27,8 @@ extern "C" int host_fold(const vdi_desc *d, const uint32_t *grid, const vdi_came
     return 0;
 }
 
-// host_tiles with the order as an argument.
-extern "C" void host_tiles_order(int W, int H, const int *r, int tw, int th, int band, int middle_out, int *placed)
+// host_tiles with the order as an argument: as previews', split frames' or exact frames' tiles.
+extern "C" void host_tiles_order(int W, int H, const int *r, int tw, int th, int band, int order, int *placed)
 {
     vdi::Frame f = {};
     f.W = W;
@@ -40,7 +40,7 @@ extern "C" void host_tiles_order(int W, int H, const int *r, int tw, int th, int
     const int nx = (W + tw - 1) / tw, n = nx * ((H + th - 1) / th);
     for (int i = 0; i < n; ++i) {
         int x0 = -1, y0 = -1;
-        const bool meets = vdi::place_tile(f, tw, th, band, i, x0, y0, middle_out != 0);
+        const bool meets = vdi::place_tile(f, tw, th, band, i, x0, y0, order == 1, order == 2);
         if (x0 < 0 || y0 < 0 || x0 >= W || y0 >= H || x0 % tw || y0 % th) continue;
         placed[(y0 / th) * nx + x0 / tw] += meets ? 100 : 101;
     }

@@ -1,6 +1,6 @@
 """Exact rays in parts folded on one lane, on the host (hipcc; nothing runs on a
 GPU): bit for bit what the parts on a lane each combine to; every tile placed
-once in both orders; the line between 32- and 64-bit plane offsets."""
+once in each order; the line between 32- and 64-bit plane offsets."""
 import ctypes
 import os
 import shutil
@@ -53,8 +53,8 @@ def test_folded_rays_are_split_rays(host, theta, alpha_max, ess):
                 assert np.array_equal(folded, split)
 
 
-@pytest.mark.parametrize("middle_out", [0, 1])
-def test_every_tile_is_placed_once_in_either_order(host, middle_out):
+@pytest.mark.parametrize("order", [0, 1, 2])
+def test_every_tile_is_placed_once_in_any_order(host, order):
     rng = np.random.default_rng(9)
     sizes = [(1, 260)] * 250 + [(600, 1400)] * 8
     for k, (lo, hi) in enumerate(sizes):
@@ -65,7 +65,7 @@ def test_every_tile_is_placed_once_in_either_order(host, middle_out):
             r[:] = 0, 0, W, H
         nx, ny = -(-W // tw), -(-H // th)
         placed = np.zeros(nx * ny, np.int32)
-        host.host_tiles_order(W, H, r.ctypes.data, tw, th, int(rng.integers(1, 9)), middle_out, placed.ctypes.data)
+        host.host_tiles_order(W, H, r.ctypes.data, tw, th, int(rng.integers(1, 9)), order, placed.ctypes.data)
         assert set(placed) <= {100, 101}, (W, H, r, tw, th)
         x, y = np.meshgrid(np.arange(nx) * tw, np.arange(ny) * th)
         meets = (x < r[2]) & (x + tw > r[0]) & (y < r[3]) & (y + th > r[1]) & (r[2] > r[0]) & (r[3] > r[1])
