@@ -90,17 +90,48 @@ int make_basis(const vdi_camera &c, Basis &b)
 
 double dot(const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
 
-// The most lists that 3 x 3 rays over the AABB's part of the image cross.
+// The most lists that 3 x 3 rays over the AABB's part of the image cross.  The
+// rays of ray_setup, plane by plane over all nine so that the loops vectorise,
+// and not normalised: a batch sets up every frame on the host before its launch
+// (ray after ray, 0.73 of the 0.92 us that a frame took; now 0.2).
 double lists_crossed(const vdi::DevVDI &V, const vdi::Frame &f)
 {
-    double most = 0.0;
-    for (int i = 0; i < 9; ++i) {
+    constexpr int N = 9;
+    double d[3][N], Xp[N], Yp[N], Zp[N], lo[N], hi[N];
+    for (int i = 0; i < N; ++i) {
         const double px = f.rx0 + (f.rx1 - f.rx0) * (0.1 + 0.4 * (i % 3)), py = f.ry0 + (f.ry1 - f.ry0) * (0.1 + 0.4 * (i / 3));
-        vdi::Ray r;
-        if (!vdi::ray_setup(f, -1.0 + 2.0 * px / f.W, -1.0 + 2.0 * py / f.H, r)) continue;
-        const double z0 = f.Z0 + r.t0 * r.Zp, z1 = f.Z0 + r.t1 * r.Zp;
-        most = std::max(most, fabs((f.X0 + r.t1 * r.Xp) / z1 - (f.X0 + r.t0 * r.Xp) / z0) * V.WO / 2 +
-                                  fabs((f.Y0 + r.t1 * r.Yp) / z1 - (f.Y0 + r.t0 * r.Yp) / z0) * V.HO / 2);
+        const double x = (-1.0 + 2.0 * px / f.W) * f.tx_n, y = (-1.0 + 2.0 * py / f.H) * f.ty_n;
+        for (int a = 0; a < 3; ++a) d[a][i] = f.FN[a] + x * f.RN[a] + y * f.UN[a];
+        Xp[i] = (f.RO[0] * d[0][i] + f.RO[1] * d[1][i] + f.RO[2] * d[2][i]) * f.sx_o;
+        Yp[i] = (f.UO[0] * d[0][i] + f.UO[1] * d[1][i] + f.UO[2] * d[2][i]) * f.sy_o;
+        Zp[i] = f.FO[0] * d[0][i] + f.FO[1] * d[1][i] + f.FO[2] * d[2][i];
+        lo[i] = f.near_n;  // F d = 1
+        hi[i] = INFINITY;
+    }
+    // Keep t with a + b t >= 0.
+    auto clip = [&](double a, const double *p, const double *q, double sp, double sq) {
+        for (int i = 0; i < N; ++i) {
+            const double b = sp * p[i] + sq * q[i], t = -a / b;
+            lo[i] = b > 0.0 && t > lo[i] ? t : lo[i];
+            hi[i] = b < 0.0 && t < hi[i] ? t : hi[i];
+            hi[i] = b == 0.0 && a < 0.0 ? -1.0 : hi[i];
+        }
+    };
+    for (int a = 0; a < 3; ++a) {
+        clip(f.eyeN[a] - f.bmin[a], d[a], d[a], 1.0, 0.0);
+        clip(f.bmax[a] - f.eyeN[a], d[a], d[a], -1.0, 0.0);
+    }
+    clip(f.Z0 - f.near_o, Zp, Zp, 1.0, 0.0);
+    clip(f.Z0 - f.X0, Zp, Xp, 1.0, -1.0);
+    clip(f.Z0 + f.X0, Zp, Xp, 1.0, 1.0);
+    clip(f.Z0 - f.Y0, Zp, Yp, 1.0, -1.0);
+    clip(f.Z0 + f.Y0, Zp, Yp, 1.0, 1.0);
+    double most = 0.0;
+    for (int i = 0; i < N; ++i) {
+        const double z0 = f.Z0 + lo[i] * Zp[i], z1 = f.Z0 + hi[i] * Zp[i];
+        const double n = fabs((f.X0 + hi[i] * Xp[i]) / z1 - (f.X0 + lo[i] * Xp[i]) / z0) * V.WO / 2 +
+                         fabs((f.Y0 + hi[i] * Yp[i]) / z1 - (f.Y0 + lo[i] * Yp[i]) / z0) * V.HO / 2;
+        if (hi[i] > lo[i] && n > most) most = n;
     }
     return most;
 }

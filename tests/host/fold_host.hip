@@ -63,3 +63,24 @@ extern "C" int host_fits32(int WO, int HO, int NS, uint64_t *o)
 }
 
 extern "C" int host_split_launch(double rays, double others) { return vdi::split_launch(rays, others); }
+
+// The lists that a frame's rays cross as its set-up estimates them, and by the
+// rays themselves.
+extern "C" int host_lists(const vdi_desc *d, const uint32_t *grid, const vdi_camera *cam, int W, int H, double *estimate,
+                          double *rays)
+{
+    HostVdi h;
+    vdi::Frame f;
+    if (load(d, grid, h) || build_frame(h.v, *cam, W, H, (double)W / H, f)) return -1;
+    *estimate = f.lists;
+    *rays = 0.0;
+    for (int i = 0; i < 9; ++i) {
+        const double px = f.rx0 + (f.rx1 - f.rx0) * (0.1 + 0.4 * (i % 3)), py = f.ry0 + (f.ry1 - f.ry0) * (0.1 + 0.4 * (i / 3));
+        vdi::Ray r;
+        if (!vdi::ray_setup(f, -1.0 + 2.0 * px / W, -1.0 + 2.0 * py / H, r)) continue;
+        const double z0 = f.Z0 + r.t0 * r.Zp, z1 = f.Z0 + r.t1 * r.Zp;
+        *rays = std::max(*rays, fabs((f.X0 + r.t1 * r.Xp) / z1 - (f.X0 + r.t0 * r.Xp) / z0) * d->width / 2 +
+                                    fabs((f.Y0 + r.t1 * r.Yp) / z1 - (f.Y0 + r.t0 * r.Yp) / z0) * d->height / 2);
+    }
+    return 0;
+}

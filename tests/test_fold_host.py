@@ -33,6 +33,8 @@ def host(tmp_path_factory):
     L.host_fold.argtypes = [ctypes.POINTER(V.Desc), P, ctypes.POINTER(V.Camera), I, I, I, I, P, P]
     L.host_tiles_order.argtypes = [I, I, P, I, I, I, I, P]
     L.host_fits32.argtypes = [I, I, I, ctypes.POINTER(ctypes.c_uint64)]
+    D = ctypes.POINTER(ctypes.c_double)
+    L.host_lists.argtypes = [ctypes.POINTER(V.Desc), P, ctypes.POINTER(V.Camera), I, I, D, D]
     L.host_split_launch.argtypes = [ctypes.c_double, ctypes.c_double]
     return L
 
@@ -94,3 +96,23 @@ def test_launches_that_split_rays(host):
     # Beside other frames, up to a million rays.
     assert f(4 * 512 * 360, 230_000) and f(850_000, 147_000) and not f(1_600_000, 276_000)
     assert not f(64 * 128 * 128, 10_000_000)
+
+
+def test_lists_crossed_is_that_of_the_rays(host):
+    v = synth.random_vdi(131, 97, 3, seed=12)
+    d, grid, _keep = bind(v)
+    rng = np.random.default_rng(13)
+    most = 0.0
+    for k in range(200):
+        a, b, rad = rng.uniform(-3, 3), rng.uniform(-1, 1), rng.uniform(0.05, 3.0)
+        target = tuple(rng.uniform(-1.0, 1.0, 3)) if k % 2 else (0.0, 0.0, 0.0)
+        cam = inputs.Camera(eye=(rad * np.sin(a), rad * b, rad * np.cos(a)), target=target, up=(0.0, 1.0, 0.0),
+                            fov_y_deg=float(rng.uniform(20, 120)))
+        if k % 20 == 0:
+            cam = inputs.orbit_camera(0.5 * k - 20.0)
+        got, want = ctypes.c_double(), ctypes.c_double()
+        assert host.host_lists(ctypes.byref(d), grid.ctypes.data, ctypes.byref(V.camera(cam)), int(rng.integers(1, 900)),
+                               int(rng.integers(1, 900)), ctypes.byref(got), ctypes.byref(want)) == 0
+        assert got.value == pytest.approx(want.value, rel=1e-9, abs=1e-9)
+        most = max(most, want.value)
+    assert most > 50.0
