@@ -376,8 +376,10 @@ typedef struct {
 } vdi_gen_params;
 
 /*
- * Generate a VDI on the device.  Per ray (all arithmetic FP64, no fused
- * multiply-adds; the per-call constants below are computed on the host):
+ * Generate a VDI on the device.  Per ray (all results as of FP64 arithmetic
+ * without fused multiply-adds: an FP32 distance only settles comparisons that
+ * it decides beyond its error bound; the per-call constants below are computed
+ * on the host):
  *   - clip to the AABB and to V_O's near plane (view depth >= near) -> [t0, t1];
  *   - N = ceil((t1 - t0)/ds - 1e-9) equal samples, clamped to
  *     [1, 2 max(nx,ny,nz) + 8], ds = longest AABB side / max(nx,ny,nz); each

@@ -597,7 +597,7 @@ hipError_t upload_set(vdi::VdiSet &S, const vdi_desc *d, bool in_place, uint64_t
     D.NS = d->max_supersegments;
     D.fmt = d->rgba_fmt_store;
     D.plane = plane;
-    D.sstride = vdi::kBrick ? (uint64_t)vdi::kBrick : plane;
+    D.sstride = vdi::kBrick;
     D.gk = d->grid_k;
     D.gnz = d->grid_nz;
     D.GW = (d->width + d->grid_k - 1) / d->grid_k;

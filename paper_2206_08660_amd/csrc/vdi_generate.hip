@@ -576,8 +576,9 @@ __host__ __device__ inline int sample_count(const GenParams &G, double t0, doubl
 // Counts come three at a time: a trial and the two that may follow it
 // (count3 fills a pass's counts, each right up to N_S and above it only known
 // to be above).  Sensitivities over `reach` (at least 2e-5, so that halving
-// towards the first trial ends), which no distance of the ray exceeds, give `runs`, the ray's runs of non-transparent samples, without a
-// pass; the first pass holds the first trial and the first two that need one.
+// towards the first trial ends), which no distance of the ray exceeds, give
+// `runs`, the ray's runs of non-transparent samples, without a pass; the first
+// pass holds the first trial and the first two that need one.
 // The lanes of a wavefront take their passes together: each first settles
 // what its counts in hand decide.
 template <typename Count3>

@@ -139,26 +139,24 @@ __host__ __device__ inline uint32_t preview_tiles(int w, int h)
 // holds four slots of depth pairs (two of colours) of a 2 x 2 block of
 // lists: the supersegments a ray meets next whether it runs along its list or
 // across neighbouring lists, and those the lanes of a tile column, which
-// cross vertically neighbouring lists in step, read together.  kBrick = 0
-// keeps whole slot planes (element j * WO * HO + li), the order of the input.
+// cross vertically neighbouring lists in step, read together.
 #ifndef VDI_BRICK
 #define VDI_BRICK 4
 #endif
 constexpr int kBrick = VDI_BRICK;
-static_assert(kBrick == 0 || (kBrick & (kBrick - 1)) == 0, "bricks must hold a power of two of lists");
+static_assert(kBrick > 0 && (kBrick & (kBrick - 1)) == 0, "bricks must hold a power of two of lists");
 
 #ifndef VDI_BRICK_W
 #define VDI_BRICK_W 2
 #endif
-constexpr int kBrickW = kBrick == 0 ? 1 : VDI_BRICK_W;
-constexpr int kBrickH = kBrick == 0 ? 1 : kBrick / kBrickW;
+constexpr int kBrickW = VDI_BRICK_W;
+constexpr int kBrickH = kBrick / kBrickW;
 
 // Storage offset of slot 0 of list (ix, iy) of a WO-wide list grid.  Idx: see
 // fits32.
 template <typename Idx = uint64_t>
 __host__ __device__ inline Idx list_base_xy(int ix, int iy, int NS, int WO)
 {
-    if constexpr (kBrick == 0) return (Idx)iy * (Idx)WO + (Idx)ix;
     const uint32_t bw = (uint32_t)(WO + kBrickW - 1) / kBrickW;
     const Idx brick = (Idx)((uint32_t)iy / kBrickH) * bw + (uint32_t)ix / kBrickW;
     return brick * ((Idx)NS * kBrick) + ((uint32_t)iy % kBrickH) * kBrickW + (uint32_t)ix % kBrickW;
@@ -170,7 +168,6 @@ __host__ __device__ inline uint64_t list_base(uint64_t li, int NS, int WO)
 // Elements of one plane set (the list grid rounded up to whole bricks, times NS).
 __host__ __device__ inline uint64_t plane_elems(int WO, int HO, int NS)
 {
-    if constexpr (kBrick == 0) return (uint64_t)WO * HO * (uint64_t)NS;
     return (uint64_t)((WO + kBrickW - 1) / kBrickW) * ((HO + kBrickH - 1) / kBrickH) * kBrick * (uint64_t)NS;
 }
 

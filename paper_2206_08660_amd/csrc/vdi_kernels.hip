@@ -469,8 +469,10 @@ __device__ __forceinline__ void persist_mirror(const PHost *ctl, const PJob *hos
     }
 }
 
-// Compiled for 5 wavefronts per SIMD (96 VGPRs): with both walkers in one
-// loop it spilled 18-48 VGPRs per lane at 6.
+// Compiled for 5 wavefronts per SIMD (96 VGPRs), where the walkers of split,
+// folded and preview rays in one loop spill 18-20 VGPRs: at 4 (128 VGPRs,
+// none) a mix of 18 requests on the 720p VDI took 0.7 ms longer, 64 exact
+// requests of 256 x 256 0.6 ms.
 #define VDI_PERSIST_OCC __attribute__((amdgpu_waves_per_eu(5)))
 
 // `mirror_jobs` and `jobs` are the same table: workgroup 0 writes it through
@@ -669,8 +671,8 @@ template <typename S, typename D, int CONV>
 __device__ __forceinline__ void scatter_tile(const S *__restrict__ src, D *__restrict__ dst, D *lds, const DevVDI &V,
                                              int x0, int y0, int j0, int nj, int top)
 {
-    static_assert(kBrick != 0, "the storage order is bricks");
     constexpr int kLists = kScatterW * kBrickH;
+    static_assert(kLists <= 256, "tile_top reads one list a thread");
     for (int s0 = 0; s0 < nj && j0 + s0 < top; s0 += kScatterSlots) {
         const int slots = min(kScatterSlots, nj - s0);
         for (int i = (int)threadIdx.x; i < kLists * slots; i += 256) {

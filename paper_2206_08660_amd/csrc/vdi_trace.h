@@ -587,12 +587,11 @@ struct Counters {
 constexpr bool kWinColour = VDI_WIN_COLOUR != 0;
 
 // Element distance between slots j and j + 1 of a list: a compile-time
-// constant with bricks, so slot addresses need no multiply.
+// constant, so slot addresses need no multiply.
 template <typename Idx>
-VDI_HD inline Idx slot_stride(const DevVDI &V)
+VDI_HD inline Idx slot_stride(const DevVDI &)
 {
-    if constexpr (kBrick != 0) return (Idx)kBrick;
-    return (Idx)V.sstride;
+    return (Idx)kBrick;
 }
 
 // Depth pair of slot j of the list whose storage starts at lb (list_base).
