@@ -2,7 +2,8 @@
 far from the volume; device planes that are not memory of the device or not
 aligned to a slot, or are still being written on the null stream; volumes with
 infinite and NaN voxels; so many small exact frames at once that their rays'
-parts are folded on one lane; a VDI too large for 32-bit offsets."""
+parts are folded on one lane; a VDI too large for 32-bit offsets; sensitivities at Eq. 1's
+own distances."""
 import ctypes
 
 import numpy as np
@@ -261,3 +262,44 @@ def test_a_vdi_too_large_for_32_bit_offsets(store):
     batched = images[1][len(singles) + 2:]
     for f, b in zip(exact[:1] + exact[1:2] + exact + previews + previews + many, batched):
         assert torch.equal(singles[id(f)], b)
+
+
+@pytest.mark.parametrize("tf,name", [(inputs.TF_KNOTS4, "knots4"), (inputs.TF_RAMP, "ramp")])
+def test_sensitivities_at_the_distances_themselves(tf, name):
+    """Eq. 1 is decided in FP32 only beyond a bound on its error.  gamma is set to distances of the generator (found
+    by bisection, to neighbouring doubles) and to both sides of them, up to where the bound ends."""
+    V = _V()
+    rng = np.random.default_rng(21)
+    vol = (0.2 + 0.6 * rng.random((32, 32, 32))).astype(np.float32)
+    bmin, bmax = inputs.aabb_for((32, 32, 32))
+    dvol = on_device(vol)
+    cam = inputs.orbit_camera(31.0)
+    W, H, ns = 12, 9, 30
+
+    def counts(gamma):
+        return inputs.generate_vdi(vol, cam, W, H, ns, tf, gamma)
+
+    gammas = []
+    pixels = np.argwhere(counts(1e-4).count > 4)
+    for y, x in pixels[rng.permutation(len(pixels))[:12]]:
+        lo, hi = 10.0 ** rng.uniform(-4, -1.5), 1.0
+        n = counts(lo).count[y, x]
+        if n == 1:
+            continue
+        while np.nextafter(lo, hi) < hi:
+            g = 0.5 * (lo + hi)
+            if counts(g).count[y, x] == n:
+                lo = g
+            else:
+                hi = g
+        gammas += [lo, hi] + [hi + s * e for e in (1e-9, 5e-8, 2e-7, 1e-6, 3.4e-6, 3.6e-6) for s in (-1, 1)]
+    assert len(gammas) > 60
+    for g in gammas:
+        if g <= 0.0:
+            continue
+        ref = counts(g)
+        got = V.generate(dvol, bmin, bmax, cam, W, H, ns, tf=name, gamma=g)
+        torch.cuda.synchronize()
+        for a, b in zip(got, (ref.count, ref.depth, ref.rgba, ref.gamma)):
+            assert np.array_equal(a.cpu().numpy(), b), g
+    print(f"[gpu] {name}: {len(gammas)} sensitivities", flush=True)
