@@ -469,8 +469,8 @@ __device__ __forceinline__ void persist_mirror(const PHost *ctl, const PJob *hos
     }
 }
 
-// Compiled for 5 wavefronts per SIMD (96 VGPRs), where the walkers of split,
-// folded and preview rays in one loop spill 18-20 VGPRs: at 4 (128 VGPRs,
+// Compiled for 5 wavefronts per SIMD (96 VGPRs), where the walkers of whole,
+// split, folded and preview rays in one loop spill 22-24 VGPRs: at 4 (128 VGPRs,
 // none) a mix of 18 requests on the 720p VDI took 0.7 ms longer, 64 exact
 // requests of 256 x 256 0.6 ms.
 #define VDI_PERSIST_OCC __attribute__((amdgpu_waves_per_eu(5)))
@@ -529,10 +529,14 @@ __global__ __launch_bounds__(kBlock) VDI_PERSIST_OCC void k_persist(const PHost 
             if (J.preview) {
                 preview_tile<FMT, uint64_t, false, true>(J.R.V, J.R.F, s_gz, (int)local);
             } else {
+                // Whole rays have a walker of their own: taken by the folding one, 60
+                // requests of mixed sizes 25.3 -> 26.2 ms, by theirs 25.5.
                 if (J.R.F.xlanes > 1)
                     split_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
-                else
+                else if (J.R.F.xparts > 1)
                     exact_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true, true>(J.R.V, J.R.F, s_gz, (int)local);
+                else
+                    exact_tile<FMT, VDI_SEARCH_WINDOW, true, uint64_t, true>(J.R.V, J.R.F, s_gz, (int)local);
             }
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores have completed
             __syncthreads();                // and s_gz is free for the next tile
